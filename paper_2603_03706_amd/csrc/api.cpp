@@ -41,6 +41,10 @@ constexpr double kMu0 = 4e-7 * M_PI;
 mm_status open_error() { return fail(MM_ERR_STATE, "the instance is in an open batch run (mm_batch_end first)"); }
 
 constexpr int kStepsPerGraph = 32;
+// Steps per launch of the whole-step kernel: a few milliseconds of work (it
+// ends by itself when its instances are done), so that the host's look at
+// the done flags between launches does not show.
+constexpr int kSmallSteps = 1024;
 // Sub-batches (streams) a new batch runs as; mm_batch_tune may choose more.
 constexpr int kDefaultParts = 1;
 constexpr int kMaxTunedParts = 3;
@@ -74,6 +78,7 @@ mm_status ensure_twiddles() {
   MM_HIP(hipMalloc(&g_twiddle, sizeof(float2) * MMI_TW_LEN));
   MM_HIP(hipMemcpy(g_twiddle, h.data(), sizeof(float2) * MMI_TW_LEN, hipMemcpyHostToDevice));
   MM_HIP(mmk_set_lds_limits());
+  MM_HIP(mmk_set_small_lds_limits());
   int dev = 0;
   MM_HIP(hipGetDevice(&dev));
   MM_HIP(hipDeviceGetAttribute(&g_cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -198,6 +203,28 @@ const char* path_name(int p) {
          : p == PATH_SPLIT  ? "split"
          : p == PATH_SPLITX ? "splitx"
                             : "fused";
+}
+
+// Instances whose RK4 steps run whole in one workgroup (k_small_rk4).  There
+// a step costs a few microseconds of dependent work on one CU, against a
+// launch of about 4 us per stage and finalisation on the per-stage path: at
+// every size whose stage inputs fit in LDS, one workgroup is the faster, alone
+// and in batches.  us per step, one workgroup vs per-stage kernels: 64 cells
+// 1.7 vs 27, 512 cells 3.0 vs 29, 1024 cells 5.1 vs 32, 2048 cells 10.4 vs 32
+// (two sublattices 16.8 vs 36, sixteen profiled modes 95 vs 117); 512
+// instances of 64 cells 2.0 vs 36, of 2048 cells 22 vs 86.
+// LDS: two stage inputs, and the mode profiles where they fit beside them.
+bool small_fits(const mm_params& p, int method, int ncell) {
+  return method == MM_RK4 && p.demag != MM_DEMAG_FFT && ncell <= MMI_SMALL_CELLS;
+}
+int small_per(int ncell) {   // cells per thread: 1, 2 or 4
+  const int per = (ncell + MMI_WG - 1) / MMI_WG;
+  return per <= 2 ? per : 4;
+}
+size_t small_lds_m(int S, int ncell) { return sizeof(float4) * 2 * (size_t)S * small_per(ncell) * MMI_WG; }
+bool small_lds_u(int S, int ncell, int N) { return small_lds_m(S, ncell) + sizeof(float) * (size_t)N * ncell <= 64 * 1024; }
+size_t small_lds(int S, int ncell, int N) {
+  return small_lds_m(S, ncell) + (small_lds_u(S, ncell, N) ? sizeof(float) * (size_t)N * ncell : 0);
 }
 
 Layout make_layout(const mm_params& p, int n_modes) {
@@ -341,7 +368,16 @@ struct mm_batch {
   hipStream_t stream = nullptr;
   InstDesc* d_desc = nullptr;
   int* d_wg = nullptr;
-  int total_wg = 0;
+  int total_wg = 0;              // entries of d_wg: the workgroups of every instance,
+  int gen_wg = 0;                // those stepped by the per-stage kernels first
+  std::vector<int> wg0;          // first entry of each instance
+  // small instances, stepped by k_small_rk4, by sublattices and cells per thread
+  struct Small {
+    int S, per, ncell = 0;       // ncell: the largest member's
+    int* list = nullptr;
+    std::vector<int> members;
+  };
+  std::vector<Small> small;
   int* d_flags = nullptr;
   int* h_flags = nullptr;
   int h_flags_local[2] = {0, 0};   // host flags of a batch without pinned memory (no-allocation run)
@@ -672,9 +708,10 @@ void batch_xfused(mm_batch* b) {
 
 InstDesc batch_desc(const mm_batch* b, int i) {
   InstDesc d = b->ctxs[i]->desc;
-  int wg0 = 0;
-  for (int j = 0; j < i; ++j) wg0 += b->ctxs[j]->desc.nwg;
-  d.wg0 = wg0;
+  const mm_ctx* c = b->ctxs[i];
+  d.wg0 = b->wg0[i];
+  d.small = small_fits(c->p, b->method, c->L.ncell) ? 1 : 0;
+  d.small_u = c->profiled && small_lds_u(d.S, d.ncell, d.N) ? 1 : 0;
   d.xfused = b->xfused.empty() ? 0 : b->xfused[i];
   if (b->rb.on) {
     for (int j = 0; j < 7; ++j) d.k[j] = b->rb.k[j];
@@ -733,12 +770,33 @@ mm_status batch_build(mm_batch* b, DevArena* arena = nullptr) {
   const bool counting = ar->mode == DevArena::COUNT;
   const int n = (int)b->ctxs.size();
   std::vector<int> wg;
-  for (int i = 0; i < n; ++i)
-    for (int w = 0; w < b->ctxs[i]->desc.nwg; ++w) wg.push_back(i);
+  b->wg0.assign(n, 0);
+  for (const bool small : {false, true}) {
+    for (int i = 0; i < n; ++i) {
+      const mm_ctx* c = b->ctxs[i];
+      if (small_fits(c->p, b->method, c->L.ncell) != small) continue;
+      b->wg0[i] = (int)wg.size();
+      for (int w = 0; w < c->desc.nwg; ++w) wg.push_back(i);
+      if (!small) continue;
+      const int per = small_per(c->L.ncell);
+      mm_batch::Small* g = nullptr;
+      for (auto& q : b->small)
+        if (q.S == c->p.sublattices && q.per == per) g = &q;
+      if (!g) {
+        b->small.push_back({c->p.sublattices, per});
+        g = &b->small.back();
+      }
+      g->members.push_back(i);
+      g->ncell = std::max(g->ncell, c->L.ncell);
+    }
+    if (!small) b->gen_wg = (int)wg.size();
+  }
   b->total_wg = (int)wg.size();
   b->arena = arena != nullptr;
   if (mm_status s = ar->take(sizeof(InstDesc) * n, (void**)&b->d_desc)) return s;
   if (mm_status s = ar->upload((void**)&b->d_wg, wg.data(), sizeof(int) * wg.size())) return s;
+  for (auto& g : b->small)
+    if (mm_status s = ar->upload((void**)&g.list, g.members.data(), sizeof(int) * g.members.size())) return s;
   if (mm_status s = ar->take(sizeof(int) * 2 * n, (void**)&b->d_flags)) return s;
   if (arena)
     b->h_flags = b->h_flags_local;
@@ -935,17 +993,39 @@ const char* final_name(int method, int st) {
 }
 
 // Stage kernel, then (unless the next y-z launch carries it) its finalisation.
+// The run start covers every instance, a step those of the per-stage kernels.
 mm_status enqueue_stage(mm_batch* b, int st, bool with_final = true) {
   const int n = (int)b->ctxs.size();
+  const int wgs = b->method == MM_RK4 && st > 0 ? b->gen_wg : b->total_wg;
   if (mm_status s = launch(b, stage_name(b->method, st), [&] {
-        return mmk_launch_stage(b->method, st, false, b->total_wg, n, b->d_desc, b->d_wg, g_twiddle,
+        return mmk_launch_stage(b->method, st, false, wgs, n, b->d_desc, b->d_wg, g_twiddle,
                                 b->stage_lds, b->stream);
       }))
     return s;
   if (!with_final) return MM_OK;
   return launch(b, final_name(b->method, st), [&] {
-    return mmk_launch_stage(b->method, st, true, b->total_wg, n, b->d_desc, b->d_wg, g_twiddle, 0, b->stream);
+    return mmk_launch_stage(b->method, st, true, wgs, n, b->d_desc, b->d_wg, g_twiddle, 0, b->stream);
   });
+}
+
+// `steps` steps of the small instances, at most kSmallSteps per launch.
+mm_status enqueue_small(mm_batch* b, int64_t steps) {
+  for (const auto& g : b->small)
+    for (const bool prof : {false, true}) {
+      size_t lds = 0;
+      for (int m : g.members) {
+        const InstDesc& d = b->ctxs[m]->desc;
+        if ((d.profiled != 0) == prof) lds = std::max(lds, small_lds(d.S, d.ncell, prof ? d.N : 0));
+      }
+      if (!lds) continue;
+      for (int64_t left = steps; left > 0; left -= kSmallSteps)
+        if (mm_status s = launch(b, "small_rk4", [&] {
+              return mmk_launch_small_rk4(g.S, g.ncell, prof, (int)g.members.size(), lds, b->d_desc, g.list,
+                                          (int)std::min<int64_t>(left, kSmallSteps), b->stream);
+            }))
+          return s;
+    }
+  return MM_OK;
 }
 
 // x-forward pass of the state for groups whose x passes run in the stage kernels
@@ -984,6 +1064,7 @@ bool merge_final(const mm_batch* b) {
 }
 
 mm_status enqueue_step(mm_batch* b) {
+  if (!b->gen_wg) return MM_OK;
   const int s0 = b->method == MM_RK4 ? 1 : 2;
   const int s1 = b->method == MM_RK4 ? 4 : 7;
   int pending = -1;
@@ -1018,13 +1099,13 @@ mm_status capture_steps(mm_batch* b, int steps, hipGraph_t* graph, hipGraphExec_
 }
 
 mm_status ensure_graph(mm_batch* b) {
-  if (b->exec) return MM_OK;
+  if (b->exec || !b->gen_wg) return MM_OK;
   return capture_steps(b, kStepsPerGraph, &b->graph, &b->exec);
 }
 
 // Graph of 2^lg steps (lg 0..4).
 mm_status ensure_graph_pow(mm_batch* b, int lg) {
-  if (b->exec_pow[lg]) return MM_OK;
+  if (b->exec_pow[lg] || !b->gen_wg) return MM_OK;
   return capture_steps(b, 1 << lg, &b->graph_pow[lg], &b->exec_pow[lg]);
 }
 
@@ -1054,11 +1135,22 @@ mm_status launch_steps(mm_batch* b, int64_t steps) {
         if (mm_status s = ensure_graph_pow(p, lg)) return s;
   }
   for (int64_t left = steps; left >= kStepsPerGraph; left -= kStepsPerGraph)
-    for (mm_batch* p : seq) MM_HIP(hipGraphLaunch(p->exec, p->stream));
+    for (mm_batch* p : seq)
+      if (p->gen_wg) MM_HIP(hipGraphLaunch(p->exec, p->stream));
   for (int lg = 4; lg >= 0; --lg)
     if ((steps % kStepsPerGraph) >> lg & 1)
-      for (mm_batch* p : seq) MM_HIP(hipGraphLaunch(p->exec_pow[lg], p->stream));
+      for (mm_batch* p : seq)
+        if (p->gen_wg) MM_HIP(hipGraphLaunch(p->exec_pow[lg], p->stream));
+  for (mm_batch* p : seq)
+    if (mm_status s = enqueue_small(p, steps)) return s;
   return MM_OK;
+}
+
+// The next piece of a run to an end time: one step graph, and as many steps
+// of the small instances (which run on by themselves where they are alone).
+mm_status launch_piece(mm_batch* b) {
+  if (b->gen_wg) MM_HIP(hipGraphLaunch(b->exec, b->stream));
+  return enqueue_small(b, b->gen_wg ? kStepsPerGraph : kSmallSteps);
 }
 
 // One reverse step of the discrete adjoint for every instance of the batch.
@@ -1223,7 +1315,7 @@ mm_status batch_run(mm_batch* b, double T, double tol, double t_end_abs = NAN) {
   if (mm_status s = ensure_graph(b)) return s;
   const int n = (int)b->ctxs.size();
   for (;;) {
-    MM_HIP(hipGraphLaunch(b->exec, b->stream));
+    if (mm_status s = launch_piece(b)) return s;
     MM_HIP(mmk_launch_gather_done(n, b->d_desc, b->d_flags, b->stream));
     MM_HIP(hipMemcpyAsync(b->h_flags, b->d_flags, sizeof(int) * 2 * n, hipMemcpyDeviceToHost, b->stream));
     MM_HIP(hipStreamSynchronize(b->stream));
@@ -1306,7 +1398,7 @@ mm_status parts_run(mm_batch* b, double T, double tol) {
   while (!active.empty()) {
     for (mm_batch* p : active) {
       const int n = (int)p->ctxs.size();
-      MM_HIP(hipGraphLaunch(p->exec, p->stream));
+      if (mm_status s = launch_piece(p)) return s;
       MM_HIP(mmk_launch_gather_done(n, p->d_desc, p->d_flags, p->stream));
       MM_HIP(hipMemcpyAsync(p->h_flags, p->d_flags, sizeof(int) * 2 * n, hipMemcpyDeviceToHost, p->stream));
     }
@@ -1374,6 +1466,12 @@ double algorithmic_bytes(const mm_batch* b, const std::string& name) {
   if (name.rfind("final_", 0) == 0) {
     double t = 0.0;   // partial records of every workgroup, read once
     for (const mm_ctx* c : b->ctxs) t += (double)c->L.nwg * MMI_PSTRIDE * sizeof(double);
+    return t;
+  }
+  if (name == "small_rk4") {   // state read and written, by the instances of that kernel
+    double t = 0.0;
+    for (const auto& g : b->small)
+      for (int m : g.members) t += 24.0 * b->ctxs[m]->L.ncell * g.S;
     return t;
   }
   const bool is_stage = name.rfind("stage_", 0) == 0;
@@ -1821,6 +1919,7 @@ mm_status mm_run_noalloc(mm_ctx* c, double T, double tol) {
   for (;;) {
     for (int k = 0; k < kStepsPerGraph; ++k)
       if (mm_status s = enqueue_step(&b)) return s;
+    if (mm_status s = enqueue_small(&b, b.gen_wg ? kStepsPerGraph : kSmallSteps)) return s;
     MM_HIP(mmk_launch_gather_done(1, b.d_desc, b.d_flags, b.stream));
     MM_HIP(hipMemcpyAsync(b.h_flags, b.d_flags, sizeof(int) * 2, hipMemcpyDeviceToHost, b.stream));
     MM_HIP(hipStreamSynchronize(b.stream));
@@ -2508,7 +2607,10 @@ mm_status mm_batch_profile(mm_batch* b, int64_t steps, double tol, int32_t cap, 
   MM_HIP(hipStreamSynchronize(b->stream));
   b->profiling = true;
   mm_status st = MM_OK;
-  for (int64_t k = 0; k < steps && st == MM_OK; ++k) st = enqueue_step(b);
+  for (int64_t k = 0; k < steps && st == MM_OK; ++k) {
+    st = enqueue_step(b);
+    if (st == MM_OK) st = enqueue_small(b, 1);
+  }
   b->profiling = false;
   hipError_t e = hipStreamSynchronize(b->stream);
   for (size_t q = 0; q < b->pending.size(); ++q) {
@@ -2851,6 +2953,8 @@ mm_status mm_batch_destroy(mm_batch* b) {
   }
   if (b->d_desc) hipFree(b->d_desc);
   if (b->d_wg) hipFree(b->d_wg);
+  for (auto& g : b->small)
+    if (g.list) hipFree(g.list);
   if (b->d_flags) hipFree(b->d_flags);
   if (b->h_flags) hipHostFree(b->h_flags);
   if (b->ev) hipEventDestroy(b->ev);

@@ -100,29 +100,14 @@ __device__ __forceinline__ Src stage_src(const InstDesc& D, CtlPtr C, int method
   return s;
 }
 
-// bdv: this cell's demag field already at hand (used when use_bdv; pass a
-// pointer fixed at compile time, never one chosen at run time, so that the
-// array stays in registers).
-// Effective field [T] on sublattice s at cell i (x, y, z its coordinates):
-// Zeeman + exchange over magnetic neighbour pairs + uniaxial anisotropy +
-// demag (local diagonal, or the FFT result in D.bd) + feedback c_s fb along
-// x + intersublattice -B_E m_{s'}.  m holds the cell's own stage input.
-template <class SRC>
-__device__ __forceinline__ void field_at(const InstDesc& D, const SRC& src, int i, int x, int y,
-                                         int z, const float (&m)[2][3], int s, float fb,
-                                         bool has_bd, float (&B)[3], const float* bdv = nullptr,
-                                         bool use_bdv = true) {
-  const int nc = D.ncell;
+// Indices of the six neighbours of cell i at (x, y, z): a missing or
+// non-magnetic neighbour is replaced by the cell itself, whose difference
+// m_j - m_i is then exactly zero, so every load of a stencil is unconditional
+// and all of them are in flight together.
+__device__ __forceinline__ void neighbours(const InstDesc& D, int i, int x, int y, int z, int (&jn)[6]) {
   const int nx = D.nx, ny = D.ny, nz = D.nz;
-  const int base = s * 3 * nc;
-  const float m0 = m[s][0], m1 = m[s][1], m2 = m[s][2];
-  float bx = D.B0x, by = D.B0y, bz = D.B0z;
-  // Neighbour indices: a missing or non-magnetic neighbour is replaced by the
-  // cell itself, whose difference m_j - m_i is then exactly zero, so every
-  // load below is unconditional and all of them are in flight together.
   const int off[6] = {-1, 1, -nx, nx, -nx * ny, nx * ny};
   const bool has[6] = {x > 0, x < nx - 1, y > 0, y < ny - 1, z > 0, z < nz - 1};
-  int jn[6];
 #pragma unroll
   for (int q = 0; q < 6; ++q) jn[q] = has[q] ? i + off[q] : i;
   if (D.has_geom) {
@@ -133,13 +118,23 @@ __device__ __forceinline__ void field_at(const InstDesc& D, const SRC& src, int 
 #pragma unroll
     for (int q = 0; q < 6; ++q) jn[q] = g[q] ? jn[q] : i;
   }
-  float nb[6][3];
-#pragma unroll
-  for (int q = 0; q < 6; ++q) {
-    nb[q][0] = src.ld(base + jn[q]);
-    nb[q][1] = src.ld(base + nc + jn[q]);
-    nb[q][2] = src.ld(base + 2 * nc + jn[q]);
-  }
+}
+
+// bdv: this cell's demag field already at hand (used when use_bdv; pass a
+// pointer fixed at compile time, never one chosen at run time, so that the
+// array stays in registers).
+// Effective field [T] on sublattice s at cell i with its neighbours' values nb:
+// Zeeman + exchange over magnetic neighbour pairs + uniaxial anisotropy +
+// demag (local diagonal, or the FFT result in D.bd) + feedback c_s fb along
+// x + intersublattice -B_E m_{s'}.  m holds the cell's own stage input.
+// DESC: InstDesc, or a copy of the members used here held in registers.
+template <class DESC>
+__device__ __forceinline__ void field_nb(const DESC& D, int i, const float (&nb)[6][3],
+                                         const float (&m)[2][3], int s, float fb,
+                                         bool has_bd, float (&B)[3], const float* bdv = nullptr,
+                                         bool use_bdv = true) {
+  const float m0 = m[s][0], m1 = m[s][1], m2 = m[s][2];
+  float bx = D.B0x, by = D.B0y, bz = D.B0z;
   const float cq[6] = {D.cex_x, D.cex_x, D.cex_y, D.cex_y, D.cex_z, D.cex_z};
   float sx = 0.f, sy = 0.f, sz = 0.f;
 #pragma unroll
@@ -168,6 +163,7 @@ __device__ __forceinline__ void field_at(const InstDesc& D, const SRC& src, int 
     bz += bdv[2];
   } else if (has_bd) {
     const MMG float* bd = gbl(D.bd);
+    const int nc = D.ncell;
     bx += gat(bd, i);
     by += gat(bd, nc + i);
     bz += gat(bd, 2 * nc + i);
@@ -182,6 +178,44 @@ __device__ __forceinline__ void field_at(const InstDesc& D, const SRC& src, int 
   B[0] = bx;
   B[1] = by;
   B[2] = bz;
+}
+
+template <class SRC>
+__device__ __forceinline__ void field_at(const InstDesc& D, const SRC& src, int i, int x, int y,
+                                         int z, const float (&m)[2][3], int s, float fb,
+                                         bool has_bd, float (&B)[3], const float* bdv = nullptr,
+                                         bool use_bdv = true) {
+  int jn[6];
+  neighbours(D, i, x, y, z, jn);
+  const int nc = D.ncell, base = s * 3 * nc;
+  float nb[6][3];
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    nb[q][0] = src.ld(base + jn[q]);
+    nb[q][1] = src.ld(base + nc + jn[q]);
+    nb[q][2] = src.ld(base + 2 * nc + jn[q]);
+  }
+  field_nb(D, i, nb, m, s, fb, has_bd, B, bdv, use_bdv);
+}
+
+// weight of a mode's profile in the feedback field: h0 Re[e^{-i Phi} a]
+__device__ __forceinline__ float feedback_weight(double h0, double cphi, double sphi, double ar, double ai) {
+  return (float)(h0 * fma(cphi, ar, sphi * ai));
+}
+
+// LL torque -gamma' [m x B + alpha m x (m x B)] in the field B
+template <class DESC>
+__device__ __forceinline__ void ll_torque(const DESC& D, const float (&m)[3], const float (&B)[3], float (&k)[3]) {
+  const float cx = m[1] * B[2] - m[2] * B[1];
+  const float cy = m[2] * B[0] - m[0] * B[2];
+  const float cz = m[0] * B[1] - m[1] * B[0];
+  const float dx = m[1] * cz - m[2] * cy;
+  const float dy = m[2] * cx - m[0] * cz;
+  const float dz = m[0] * cy - m[1] * cx;
+  const float a = D.alpha, gl = -D.gl;
+  k[0] = gl * fmaf(a, dx, cx);
+  k[1] = gl * fmaf(a, dy, cy);
+  k[2] = gl * fmaf(a, dz, cz);
 }
 
 // The workgroups of one dispatch are placed on the eight XCDs round-robin
@@ -272,6 +306,17 @@ __device__ __forceinline__ double wave_sum(double v) {
   v = a + b;
   if constexpr (O > 1) return wave_sum<O / 2>(v);
   else return v;
+}
+
+// The wave sums of two values: a's in lanes 0-31, b's in lanes 32-63, each
+// with the additions of wave_sum in its order.  After the exchange over 32
+// lanes the halves hold the same values, so one chain of steps serves both.
+__device__ __forceinline__ double wave_sum2(double u, double v) {
+  double a, b, c, d;
+  lane_pair<32>(u, a, b);
+  lane_pair<32>(v, c, d);
+  const double su = a + b, sv = c + d;
+  return wave_sum<16>((threadIdx.x & 32) ? sv : su);
 }
 
 template <int O = 32>

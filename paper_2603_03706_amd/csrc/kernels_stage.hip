@@ -20,18 +20,7 @@ __device__ __forceinline__ void torque_at(const InstDesc& D, const SRC& src, int
                                           bool use_bdv = true) {
   float B[3];
   field_at(D, src, i, x, y, z, m, s, fb, has_bd, B, bdv, use_bdv);
-  const float m0 = m[s][0], m1 = m[s][1], m2 = m[s][2];
-  // -gl [m x B + alpha m x (m x B)]
-  const float cx = m1 * B[2] - m2 * B[1];
-  const float cy = m2 * B[0] - m0 * B[2];
-  const float cz = m0 * B[1] - m1 * B[0];
-  const float dx = m1 * cz - m2 * cy;
-  const float dy = m2 * cx - m0 * cz;
-  const float dz = m0 * cy - m1 * cx;
-  const float a = D.alpha, gl = -D.gl;
-  k[0] = gl * fmaf(a, dx, cx);
-  k[1] = gl * fmaf(a, dy, cy);
-  k[2] = gl * fmaf(a, dz, cz);
+  ll_torque(D, m[s], B, k);
 }
 
 
@@ -129,7 +118,7 @@ __global__ __launch_bounds__(MMI_WG) void k_stage(const InstDesc* __restrict__ d
   float fbc[MMI_MAX_MODES];
   const int NM = D.N;
   for (int n = 0; n < MMI_MAX_MODES; ++n)
-    fbc[n] = n < NM ? (float)(D.h0[n] * (D.cphi[n] * C->as[n][0] + D.sphi[n] * C->as[n][1])) : 0.f;
+    fbc[n] = n < NM ? feedback_weight(D.h0[n], D.cphi[n], D.sphi[n], C->as[n][0], C->as[n][1]) : 0.f;
 
   // only the DP45 stage-2 input is formed on the fly from two fields
   const SrcFixed<METHOD == MMI_DP45 && ST == 2> src(stage_src(D, C, METHOD, ST));

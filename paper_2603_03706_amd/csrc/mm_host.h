@@ -17,6 +17,11 @@ hipError_t mmk_launch_xfwd_cells(int method, int stage, int nblocks, const InstD
 hipError_t mmk_launch_stage(int method, int stage, bool final_pass, int nblocks, int count,
                             const InstDesc* descs, const int* wg, const float2* tw, size_t lds,
                             hipStream_t stream);
+// `steps` whole RK4 steps of nblocks small instances (indices in list), each of S sublattices and at most ncell
+// (<= MMI_SMALL_CELLS) cells; profiled: steps those with mode profiles, else those without; lds: dynamic LDS, the largest of the instances'
+hipError_t mmk_launch_small_rk4(int S, int ncell, bool profiled, int nblocks, size_t lds, const InstDesc* d, const int* list, int steps,
+                                hipStream_t s);
+hipError_t mmk_set_small_lds_limits();
 // x passes with lines in registers: Px = 4 MX, MX in {4, 8, 16, 32}; dir +1 forward (method,
 // stage select the stage input), -1 inverse; work items are tiles of 128 rows
 hipError_t mmk_launch_fft_xr(int dir, int MX, int nblocks, const InstDesc* d, const WorkItem* w, int method,

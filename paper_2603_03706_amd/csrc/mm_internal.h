@@ -8,6 +8,8 @@
 #define MMI_LG_WG 9
 #define MMI_PSTRIDE 72             // doubles per workgroup partial record
 #define MMI_TW_LEN 1024            // length of the twiddle table (max FFT length)
+#define MMI_SMALL_CELLS 2048       // largest instance the whole-step kernel carries (k_small_rk4)
+#define MMI_SMALL_LDS (136 * 1024) // dynamic LDS of that kernel at most
 
 // partial-record slots (doubles)
 //   [0, 2N)       sum of u_n * m^- of the next stage input (re, im)
@@ -67,7 +69,9 @@ struct InstDesc {
   int lgnx, lgny;                     // log2 of nx, ny when powers of two, else -1
   int S, N, profiled, has_geom;
   int demag, method, nwg, wg0;
-  int split, pad_split;               // RK4 in the operator-split scheme (cavity first, m^- held)
+  int split;                          // RK4 in the operator-split scheme (cavity first, m^- held)
+  int small;                          // steps run in k_small_rk4: the per-stage kernels skip the instance
+  int small_u, pad_small;             // k_small_rk4 keeps the mode profiles in LDS
   float cex_x, cex_y, cex_z;          // (2A/Ms)/d^2 per axis
   float cK, ex, ey, ez;               // 2K/Ms and the unit axis
   float B0x, B0y, B0z;

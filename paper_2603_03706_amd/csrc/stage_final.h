@@ -9,46 +9,63 @@
 
 namespace mmk {
 
+__device__ __forceinline__ void cav_sincos(const InstDesc&, double x, double& sn, double& cs) { sincos(x, &sn, &cs); }
+
+// envelope of the Gaussian drive of mode n at time t
+__device__ __forceinline__ double gauss_envelope(double t, double t0, double sigma) {
+#pragma clang fp contract(off)
+  const double x = (t - t0) / sigma;
+  return exp(-0.5 * x * x);
+}
+__device__ __forceinline__ double cav_envelope(const InstDesc& D, int n, double t) {
+  return gauss_envelope(t, D.eta_t0[n], D.eta_sigma[n]);
+}
+
 // Cavity right-hand side of mode n at stage time t, with the stage
 // amplitudes of all modes in A: (-i w - kappa) a + i g e^{-i Phi} m^-
 // (Eq. (12) with the phase of Eq. (19)), plus, when set, the self-Kerr term
 // -i K |a|^2 a, the direct mode coupling -i sum_m J_nm a_m (the H_13 entry of
 // Eq. (14)), the degenerate parametric pump -i lam e^{-2 i wp t} conj(a) and
-// the Gaussian drive eta_n(t) of Eq. (1).
-__device__ __forceinline__ void cav_rhs(const InstDesc& D, int n, double t, const double (*A)[2],
+// the Gaussian drive eta_n(t) of Eq. (1).  DESC: InstDesc, or one mode's
+// parameters held in registers behind the same names.
+// AMP: the stage amplitudes, A[mode][re/im].
+template <class DESC, class AMP>
+__device__ __forceinline__ void cav_rhs(const DESC& D, int n, double t, const AMP& A,
                                         double mr, double mi, double& fr, double& fi) {
+  // every fused multiply-add is written out, so that each kernel this is
+  // inlined into rounds alike
+#pragma clang fp contract(off)
   const double ar = A[n][0], ai = A[n][1];
   const double w = D.omega[n], kp = D.kappa[n], g = D.g[n], c = D.cphi[n], s = D.sphi[n];
-  fr = -kp * ar + w * ai + g * (s * mr - c * mi);
-  fi = -w * ar - kp * ai + g * (s * mi + c * mr);
+  fr = fma(g, fma(s, mr, -(c * mi)), fma(w, ai, -(kp * ar)));
+  fi = fma(g, fma(s, mi, c * mr), -fma(w, ar, kp * ai));
   if (D.kerr_on) {
-    const double q = D.kerr[n] * (ar * ar + ai * ai);
-    fr += q * ai;
-    fi -= q * ar;
+    const double q = D.kerr[n] * fma(ar, ar, ai * ai);
+    fr = fma(q, ai, fr);
+    fi = fma(-q, ar, fi);
   }
   if (D.jcpl_on) {
     double jr = 0.0, ji = 0.0;
     for (int m = 0; m < D.N; ++m) {
-      jr += D.jcpl[n][m] * A[m][0];
-      ji += D.jcpl[n][m] * A[m][1];
+      jr = fma(D.jcpl[n][m], A[m][0], jr);
+      ji = fma(D.jcpl[n][m], A[m][1], ji);
     }
     fr += ji;
     fi -= jr;
   }
   if (D.param_on) {
     double sn, cs;
-    sincos(2.0 * D.par_wp[n] * t, &sn, &cs);
+    cav_sincos(D, 2.0 * D.par_wp[n] * t, sn, cs);
     // Lam = lam e^{-2 i wp t};  -i Lam conj(a) = (Li ar - Lr ai) - i (Lr ar + Li ai)
-    const double lr = D.par_re[n] * cs + D.par_im[n] * sn;
-    const double li = D.par_im[n] * cs - D.par_re[n] * sn;
-    fr += li * ar - lr * ai;
-    fi -= lr * ar + li * ai;
+    const double lr = fma(D.par_re[n], cs, D.par_im[n] * sn);
+    const double li = fma(D.par_im[n], cs, -(D.par_re[n] * sn));
+    fr += fma(li, ar, -(lr * ai));
+    fi -= fma(lr, ar, li * ai);
   }
   if (D.drive_on) {
-    const double x = (t - D.eta_t0[n]) / D.eta_sigma[n];
-    const double e = exp(-0.5 * x * x);
-    fr += D.eta_re[n] * e;
-    fi += D.eta_im[n] * e;
+    const double e = cav_envelope(D, n, t);
+    fr = fma(D.eta_re[n], e, fr);
+    fi = fma(D.eta_im[n], e, fi);
   }
 }
 
@@ -452,6 +469,7 @@ __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double*
   const InstDesc& D = descs[inst];
   InstCtl* C = D.ctl;
   if (C->done) return;
+  if (METHOD == MMI_RK4 && ST >= 1 && D.small) return;
   const bool has_next = !(METHOD == MMI_DP45 && ST == 7);
   const double scale = D.inv_ngeo / (double)D.S;
   // the slots this stage needs, dealt to the waves as one list so that the
