@@ -304,7 +304,7 @@ mm_status mm_batch_tune_fft(mm_batch* b, char* report, size_t report_len);
 
 /* Demag y-z strategy for every FFT grid shape in the batch (mm_batch_tune
  * chooses one per shape by timing; before that the exchange strategy is used
- * where it applies, else the eight-lane register one, else the register one,
+ * where it applies, else the halved one, else the eight-lane register one, else the register one,
  * else the fused one where it fits, else the split exchange one, else the
  * split one):
  *   MM_YZ_FUSED     y and z lines transformed in LDS by one workgroup per
@@ -321,6 +321,10 @@ mm_status mm_batch_tune_fft(mm_batch* b, char* report, size_t report_len);
  *   MM_YZ_SPLIT_EXCHANGE  the split passes with the y passes done by the
  *                   line transforms of MM_YZ_EXCHANGE (whole rows per lane
  *                   group) and the z pass of MM_YZ_SPLIT; padded y of 16..256.
+ *   MM_YZ_HALVES    one workgroup per (instance, kx, parity of ky), each with
+ *                   the row and column transforms of MM_YZ_EXCHANGE on half
+ *                   the ky range; padded y of 64..256, padded z of 32 or 64,
+ *                   nx >= 2.
  * All of them compute the same convolution (agreement to FP32 rounding).
  * Returns MM_ERR_ARG, changing nothing, if some shape cannot use `path`. */
 enum {
@@ -329,7 +333,8 @@ enum {
   MM_YZ_SPLIT = 2,
   MM_YZ_REGISTER8 = 3,
   MM_YZ_EXCHANGE = 4,
-  MM_YZ_SPLIT_EXCHANGE = 5
+  MM_YZ_SPLIT_EXCHANGE = 5,
+  MM_YZ_HALVES = 6
 };
 mm_status mm_batch_set_fft_path(mm_batch* b, int32_t path);
 

@@ -166,7 +166,8 @@ enum {
   PATH_SPLIT = MM_YZ_SPLIT,
   PATH_REG8 = MM_YZ_REGISTER8,
   PATH_XCH = MM_YZ_EXCHANGE,
-  PATH_SPLITX = MM_YZ_SPLIT_EXCHANGE
+  PATH_SPLITX = MM_YZ_SPLIT_EXCHANGE,
+  PATH_HALVES = MM_YZ_HALVES
 };
 // eight lanes per z column: padded z of 32 or 64
 bool reg8_fits(int ny, int nz, int py, int pz) { return reg_fits(ny, nz, py, pz) && (pz == 32 || pz == 64); }
@@ -179,6 +180,8 @@ size_t xch_lds(int py, int pz) {
 // split passes with the two-pass y line transforms: padded y of 16..256
 bool splitx_fits(int py) { return mmk_sx_rows(py) > 0; }
 size_t splitx_lds_y(int py) { return sizeof(float2) * ((size_t)mmk_sx_rows(py) * (py + 1) + py); }
+// two halves of the ky range per plane: padded y of 64..256, padded z of 32 or 64, at least three kx planes
+bool halves_fits(int py, int pz, int kx) { return kx >= 3 && mmk_yzh_lds(py, pz) > 0; }
 bool xch_fits(int ny, int nz, int py, int pz) {
   (void)ny, (void)nz;
   const bool y_ok = py == 16 || py == 32 || py == 64 || py == 128;
@@ -202,6 +205,7 @@ const char* path_name(int p) {
          : p == PATH_XCH    ? "xch"
          : p == PATH_SPLIT  ? "split"
          : p == PATH_SPLITX ? "splitx"
+         : p == PATH_HALVES ? "halves"
                             : "fused";
 }
 
@@ -416,6 +420,7 @@ struct mm_batch {
   hipGraph_t graph_rev = nullptr;
   hipEvent_t ev = nullptr;
   std::vector<int> xfused;     // per instance: x passes inside the stage kernels
+  std::vector<int> yzh;        // per instance: convolved rows in two terms (PATH_HALVES)
   size_t stage_lds = 0;        // dynamic LDS of the stage kernels (x passes), 0 if none
   // profiling
   bool profiling = false;
@@ -665,11 +670,16 @@ mm_status build_group(mm_batch::Group& g, DevArena* arena = nullptr) {
   // item (item 0), which takes longer than the others: these items go first,
   // so that none of them starts in the launch's last round.
   const bool pairs = g.path == PATH_XCH && g.kx > 1 && mmk_yzx_pairs(g.py, g.pz);
-  if (pairs)
+  const bool halves = g.path == PATH_HALVES;
+  if (pairs || halves)
     for (int m : g.members) yz.push_back({m, 0});
+  if (halves)
+    for (int m : g.members) yz.push_back({m, 1});
   for (int m : g.members) {
     for (int t = 0; t < tiles_x; ++t) xf.push_back({m, t});
-    if (g.path != PATH_SPLIT && !sx) {
+    if (halves) {
+      for (int k = 2; k < 2 * (g.kx - 1); ++k) yz.push_back({m, k});
+    } else if (g.path != PATH_SPLIT && !sx) {
       for (int k = pairs ? 1 : 0; k < (pairs ? g.kx - 1 : g.kx); ++k) yz.push_back({m, k});
     } else {
       for (int t = 0; t < tiles_y; ++t) yy.push_back({m, t});
@@ -687,7 +697,8 @@ mm_status build_group(mm_batch::Group& g, DevArena* arena = nullptr) {
   if (mm_status s = up(zc, &g.zc, &g.n_zc)) return s;
   g.lds_xf = g.Wx == 0 ? 0 : sizeof(float2) * ((size_t)g.px * (g.Wx + 1) + g.px);
   g.lds_xi = g.Wx == 0 ? 0 : sizeof(float2) * ((size_t)g.px * (g.Wx + 1) + (size_t)g.kx * 2 * g.Wx + g.px);
-  g.lds_yz = g.path == PATH_XCH                             ? xch_lds(g.py, g.pz)
+  g.lds_yz = halves                                         ? mmk_yzh_lds(g.py, g.pz)
+             : g.path == PATH_XCH                           ? xch_lds(g.py, g.pz)
              : (g.path == PATH_REG || g.path == PATH_REG8) ? reg_lds(g.nz, g.py, g.pz)
                                                            : fused_lds(g.ny, g.nz, g.py, g.pz, g.TK);
   g.lds_y = sx ? splitx_lds_y(g.py) : sizeof(float2) * ((size_t)g.py * (g.Wy + 1) + g.py);
@@ -695,10 +706,14 @@ mm_status build_group(mm_batch::Group& g, DevArena* arena = nullptr) {
   return MM_OK;
 }
 
-// Per-instance x-pass placement and the stage kernels' LDS, from the groups.
+// Per-instance x-pass placement, form of the convolved rows and the stage kernels' LDS, from the groups.
 void batch_xfused(mm_batch* b) {
   b->xfused.assign(b->ctxs.size(), 0);
+  b->yzh.assign(b->ctxs.size(), 0);
   b->stage_lds = 0;
+  for (auto& g : b->groups)
+    if (g.path == PATH_HALVES)
+      for (int m : g.members) b->yzh[m] = 1;
   for (auto& g : b->groups)
     if (g.xfused) {
       for (int m : g.members) b->xfused[m] = 1;
@@ -713,6 +728,7 @@ InstDesc batch_desc(const mm_batch* b, int i) {
   d.small = small_fits(c->p, b->method, c->L.ncell) ? 1 : 0;
   d.small_u = c->profiled && small_lds_u(d.S, d.ncell, d.N) ? 1 : 0;
   d.xfused = b->xfused.empty() ? 0 : b->xfused[i];
+  d.yzh = !b->yzh.empty() && b->yzh[i] ? c->L.kx * 3 * c->p.nz * c->p.ny : 0;
   if (b->rb.on) {
     for (int j = 0; j < 7; ++j) d.k[j] = b->rb.k[j];
     for (int j = 0; j < 2; ++j) d.st[j] = b->rb.st[j];
@@ -751,8 +767,9 @@ mm_status carve_run_buffers(mm_batch* b, DevArena* ar) {
     const mm_params& p = c->p;
     if (mm_status s = ar->take(sizeof(float) * 3 * (size_t)L.ncell, (void**)&r.bd)) return s;
     if (mm_status s = ar->take(sizeof(float2) * (size_t)L.kx * 3 * p.nz * p.ny, (void**)&r.fx)) return s;
-    // the spectra of the y pass exist only on the split y-z paths
-    if (!b->groups.empty() && (b->groups[0].path == PATH_SPLIT || b->groups[0].path == PATH_SPLITX))
+    // the y pass's spectra (split y-z paths) or the convolved rows' two terms
+    if (!b->groups.empty() && (b->groups[0].path == PATH_SPLIT || b->groups[0].path == PATH_SPLITX ||
+                               b->groups[0].path == PATH_HALVES))
       if (mm_status s = ar->take(sizeof(float2) * (size_t)L.kx * 3 * p.nz * L.py, (void**)&r.fy)) return s;
   }
   r.on = true;
@@ -815,7 +832,12 @@ mm_status batch_build(mm_batch* b, DevArena* arena = nullptr) {
       g = &b->groups.back();
       g->nx = c->p.nx; g->ny = c->p.ny; g->nz = c->p.nz;
       g->px = c->L.px; g->py = c->L.py; g->pz = c->L.pz; g->kx = c->L.kx;
-      g->path = xch_fits(g->ny, g->nz, g->py, g->pz)    ? PATH_XCH
+      // The exchange kernel holds a whole plane; where that fills a CU's LDS
+      // (128 x 64) or exceeds it (256 x 64), halves are the faster, and 256 x 32
+      // goes with them.  us per launch: 101 planes' worth of 100x60x20 16.4 vs
+      // 18.9, the 128x128x32 film 28.6 vs 53.7 in split passes.
+      g->path = halves_fits(g->py, g->pz, g->kx) && (g->py == 256 || (g->py == 128 && g->pz == 64)) ? PATH_HALVES
+                : xch_fits(g->ny, g->nz, g->py, g->pz)  ? PATH_XCH
                 : reg8_fits(g->ny, g->nz, g->py, g->pz) ? PATH_REG8
                 : reg_fits(g->ny, g->nz, g->py, g->pz)  ? PATH_REG
                 : c->L.split && splitx_fits(g->py)     ? PATH_SPLITX
@@ -923,7 +945,13 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
           return mmk_launch_fft_xf(g.Wx, g.n_xf, g.lds_xf, b->d_desc, g.xf, method, stage, g_twiddle, b->stream);
         }))
       return s;
-    if (g.path == PATH_REG8 || g.path == PATH_XCH) {
+    if (g.path == PATH_HALVES) {
+      if (mm_status s = launch(b, "fft_yz_convolve", [&] {
+            return mmk_launch_fft_yzh(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
+                                      first ? nfinal : 0, b->method, final_st);
+          }))
+        return s;
+    } else if (g.path == PATH_REG8 || g.path == PATH_XCH) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
             auto f = g.path == PATH_XCH ? mmk_launch_fft_yzx : mmk_launch_fft_yz8;
             return f(g.py / 4, g.pz / 4, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
@@ -1060,7 +1088,7 @@ mm_status enqueue_start(mm_batch* b) {
 bool merge_final(const mm_batch* b) {
   if (b->groups.empty()) return false;
   const int p = b->groups[0].path;
-  return p == PATH_REG8 || p == PATH_XCH || p == PATH_SPLITX;
+  return p == PATH_REG8 || p == PATH_XCH || p == PATH_HALVES || p == PATH_SPLITX;
 }
 
 mm_status enqueue_step(mm_batch* b) {
@@ -2513,7 +2541,7 @@ mm_status mm_batch_end(mm_batch* b) {
 
 static mm_status check_fft_path(const mm_batch* b, int32_t path) {
   if (path != PATH_FUSED && path != PATH_REG && path != PATH_SPLIT && path != PATH_REG8 && path != PATH_XCH &&
-      path != PATH_SPLITX)
+      path != PATH_SPLITX && path != PATH_HALVES)
     return fail(MM_ERR_ARG, "unknown y-z path");
   for (const mm_batch* p : b->parts)
     if (mm_status s = check_fft_path(p, path)) return s;
@@ -2526,6 +2554,8 @@ static mm_status check_fft_path(const mm_batch* b, int32_t path) {
       return fail(MM_ERR_ARG, "split exchange y-z path needs padded y in 16..256");
     if (path == PATH_XCH && !xch_fits(g.ny, g.nz, g.py, g.pz))
       return fail(MM_ERR_ARG, "exchange y-z path needs padded y in 16..128 and padded z of 32 or 64");
+    if (path == PATH_HALVES && !halves_fits(g.py, g.pz, g.kx))
+      return fail(MM_ERR_ARG, "halved y-z path needs padded y in 64..256, padded z of 32 or 64 and two or more cells along x");
     if (path == PATH_FUSED && !fused_fits(g.ny, g.nz, g.py, g.pz))
       return fail(MM_ERR_ARG, "fused y-z path does not fit in LDS for this grid");
   }
@@ -2545,6 +2575,8 @@ mm_status mm_batch_set_fft_path(mm_batch* b, int32_t path) {
     if (path == PATH_FUSED) g.TK = std::max(1, fused_tile(g.ny, g.nz, g.py, g.pz));
     if (mm_status s = build_group(g)) return s;
   }
+  batch_xfused(b);
+  if (mm_status s = upload_batch_descs(b)) return s;
   drop_graphs(b);
   return MM_OK;
 }
@@ -2876,6 +2908,17 @@ static mm_status tune_fft(mm_batch* b, std::string& out) {
       yrep += (yrep.empty() ? "" : ", ") + std::string("\"xch\": ") + std::to_string(us);
       if (us < bestYZ) { bestYZ = us; bestPath = PATH_XCH; }
     }
+    if (halves_fits(g.py, g.pz, g.kx)) {
+      g.path = PATH_HALVES;
+      if (mm_status s = build_group(g)) return s;
+      double us;
+      if (mm_status s = timed([&] {
+            return mmk_launch_fft_yzh(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream);
+          }, &us))
+        return s;
+      yrep += (yrep.empty() ? "" : ", ") + std::string("\"halves\": ") + std::to_string(us);
+      if (us < bestYZ) { bestYZ = us; bestPath = PATH_HALVES; }
+    }
     for (int TW = 1; TW <= 16 && splitx_fits(g.py); TW *= 2) {
       if (sizeof(float2) * ((size_t)g.pz * 3 * TW + g.pz) > lds_cap) continue;
       g.path = PATH_SPLITX;
@@ -2929,6 +2972,9 @@ static mm_status tune_fft(mm_batch* b, std::string& out) {
   rep += "]";
   hipEventDestroy(e0);
   hipEventDestroy(e1);
+  batch_xfused(b);
+  MM_HIP(hipStreamSynchronize(b->stream));
+  if (mm_status s = upload_batch_descs(b)) return s;
   // launch sequences changed: recapture on next use
   drop_graphs(b);
   MM_HIP(hipStreamSynchronize(b->stream));

@@ -218,6 +218,19 @@ __device__ __forceinline__ void ll_torque(const DESC& D, const float (&m)[3], co
   k[2] = gl * fmaf(a, dz, cz);
 }
 
+// Convolved x-transformed rows: in place in D.fx, or (D.yzh) as two terms in
+// D.fy, one after the other, to be added.  e: element of [kx][c][z][y].
+__device__ __forceinline__ const MMG float2* conv_rows(const InstDesc& D) { return gbl(D.yzh ? D.fy : D.fx); }
+__device__ __forceinline__ float2 conv_row(const InstDesc& D, const MMG float2* X, int e) {
+  float2 v = gld2(&gat(X, e));
+  if (D.yzh) {
+    const float2 w = gld2(&gat(X, e + D.yzh));
+    v.x += w.x;
+    v.y += w.y;
+  }
+  return v;
+}
+
 // The workgroups of one dispatch are placed on the eight XCDs round-robin
 // (block b on XCD b mod 8) and every XCD has its own L2.  This maps the
 // hardware block index to a logical one (a bijection on [0, gridDim.x)) so

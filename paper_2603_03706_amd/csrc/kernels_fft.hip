@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void k_fft_xi(const InstDesc* __restrict__ des
   float2* twl = stg + Kx * 2 * W;
   load_twiddles(twl, Px, tw, 256);
   // batches of 8 loads per thread in flight (clamped addresses, padding selected afterwards)
-  const MMG float2* fx = gbl(D.fx);
+  const MMG float2* fx = conv_rows(D);
   for (int e0 = 0; e0 < Kx * 2 * W; e0 += 8 * 256) {
     float2 v[8];
 #pragma unroll
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(256) void k_fft_xi(const InstDesc* __restrict__ des
       const int kx = min(e / (2 * W), Kx - 1), rr = e - (e / (2 * W)) * 2 * W;
       const int r = r0 + rr;
       const bool in = e < Kx * 2 * W && r < rows;
-      const float2 t = gld2(fx + (size_t)kx * rows + min(r, rows - 1));
+      const float2 t = conv_row(D, fx, kx * rows + min(r, rows - 1));
       v[u] = make_float2(in ? t.x : 0.f, in ? t.y : 0.f);
     }
 #pragma unroll
@@ -677,7 +677,6 @@ __device__ __forceinline__ void quad_inverse8(const float2 (&w)[M], int r, float
 // blocks of the previous stage kernel, which the transform never touches, so
 // the two share one launch and the finalisation fills the last, partly empty
 // round of transform workgroups.
-static_assert(MM_YZ8_T == MMI_WG, "the finalisation body assumes MMI_WG threads");
 
 template <int MY, int MZ>
 __global__ __launch_bounds__(MM_YZ8_T) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_fft_yz8(const InstDesc* __restrict__ descs,
@@ -863,7 +862,6 @@ __global__ __launch_bounds__(MM_YZ8_T) __attribute__((amdgpu_waves_per_eu(4, 4))
 //   per ky column: forward z of the three components, kernel multiply,
 //   inverse z (in place);  inverse y per row (in place);  store X.
 #define MM_YZX_T 512
-static_assert(MM_YZX_T == MMI_WG, "the finalisation body in the extra workgroups assumes MMI_WG threads");
 
 // points per lane Q and lanes per line L of a padded length P (Q >= L):
 // y rows take up to sixteen points per lane, z columns eight
@@ -1422,6 +1420,399 @@ __global__ __launch_bounds__(MM_YZX_T) __attribute__((amdgpu_waves_per_eu(MY >= 
   yzx_item<MY, MZ, RPAD, false>(D, wi.item, tw, lds);
 }
 
+// ---------------- y-z in two halves of the ky range (frequency residues)
+// A padded y line of length 2M whose inputs vanish from M on splits by the
+// residue r of its frequency index, without any zeros left over:
+//   X[2k + r] = sum_{j < M} (W_2M^{rj} x[j]) W_M^{jk},
+// and the cropped inverse is the sum over r of W_2M^{-rj} times the M-point
+// inverse transform of X[2k + r].  A work item is (instance, kx, r): it takes
+// the rows' M-point transforms, convolves its M columns along z, transforms
+// back, and writes its term of the sum; whoever reads the convolved rows
+// (the stage kernels' C2R) adds the two terms.  Rows, columns and kernel
+// values of an item are half those of the whole plane, so padded planes of
+// 256 x 64, whose rows alone exceed LDS, are done in one pass over X, and
+// planes that fit are spread over twice the workgroups.
+// Items write to D.fy ([r][kx][c][z][y], y < ny): both read the same X.
+//
+// What bounds it: the phases of one workgroup (256 x 64: 153 KB of LDS, one per
+// CU), which the launch is a single round of.  Of an ordinary item's 19 us at
+// 128 x 128 x 32 cells 3.7 go to loading rows and kernel values, 3.1 to each y
+// pass, 6 to the z convolution, 2.3 to the store; vector issue alone would be 13.
+// The launch (28.6 us against 53.7 for the three split passes, which moved
+// the padded spectra through memory twice) waits for the two items that carry
+// the real planes: separating and rebuilding their half spectra and the
+// second kernel slice make them a third longer.  Reading that slice from
+// memory in the multiply (38 us), or replacing the first one in LDS between
+// the halves of the workgroup (35 us), was slower than putting it where the
+// rows were.
+
+// M-point transforms of one row of M slots by N lanes (lane lam), in place;
+// twm: W_M in LDS.
+template <int M>
+struct YFull {
+  static constexpr int Q = 16, N = M / Q, lgQ = 4, lgN = ilog2c(N);
+  static_assert(N >= 2 && N <= Q, "row length");
+  __device__ static void forward(float2* line, int lam, const float2* twm) {
+    float2 v[Q];
+#pragma unroll
+    for (int n1 = 0; n1 < Q; ++n1) v[n1] = line[N * n1 + lam];
+    dif_stages<Q, false, Q / 2>(v);
+    wave_lds_order();
+#pragma unroll
+    for (int p = 0; p < Q; ++p) {
+      const int k1 = brevc(p, lgQ);
+      line[xslot<N>(k1, lam)] = k1 ? cmul(v[p], twm[lam * k1]) : v[p];
+    }
+    wave_lds_order();
+    float2 u[Q / N][N];
+#pragma unroll
+    for (int j = 0; j < Q / N; ++j) {
+#pragma unroll
+      for (int a = 0; a < N; ++a) u[j][a] = line[xslot<N>(lam + N * j, a)];
+      dif_stages<N, false, N / 2>(u[j]);
+    }
+    wave_lds_order();
+#pragma unroll
+    for (int j = 0; j < Q / N; ++j)
+#pragma unroll
+      for (int p = 0; p < N; ++p) line[lam + N * j + Q * brevc(p, lgN)] = u[j][p];
+  }
+  // Row of A + iB (A, B real rows before the twist by W_2M^{rj}) to their
+  // spectra: A[k] = (X[k] + conj X[k']) / 2, B[k] = (X[k] - conj X[k']) / 2i
+  // with k' = M - k (r = 0) or M - 1 - k (r = 1), k < M/2, at slots
+  // SM::of(0, k) and SM::of(1, k); for r = 0 the real values at k = 0 and M/2
+  // share the slots of k = 0.
+  template <class SM>
+  __device__ static void split_pair(float2* line, int lam, int r) {
+    constexpr int H = M / 2, NI = H / N;
+    float2 x[NI], q[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int k = lam + N * i;
+      x[i] = line[k];
+      q[i] = line[r ? M - 1 - k : k == 0 ? H : M - k];
+    }
+    wave_lds_order();
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int k = lam + N * i;
+      const bool z = !r && k == 0;
+      line[SM::of(0, k)] = z ? make_float2(x[i].x, q[i].x) : make_float2(0.5f * (x[i].x + q[i].x), 0.5f * (x[i].y - q[i].y));
+      line[SM::of(1, k)] = z ? make_float2(x[i].y, q[i].y) : make_float2(0.5f * (x[i].y + q[i].y), 0.5f * (q[i].x - x[i].x));
+    }
+  }
+  // spectrum of A + iB at k from the two half spectra
+  template <class SM>
+  __device__ static float2 pair_value(const float2* line, int k, int r) {
+    constexpr int H = M / 2;
+    const bool lo = k < H;
+    const int m = lo ? k : r ? M - 1 - k : M - k;
+    const int i = m == H ? 0 : m;                 // (r = 0, k = M/2: the shared slot)
+    const float2 a = line[SM::of(0, i)], b = line[SM::of(1, i)];
+    if (!r && k == 0) return make_float2(a.x, b.x);
+    if (m == H) return make_float2(a.y, b.y);
+    return lo ? make_float2(a.x - b.y, a.y + b.x) : make_float2(a.x + b.y, b.x - a.y);
+  }
+  template <class SM = void>
+  __device__ static void inverse(float2* line, int lam, const float2* twm, int r) {
+    float2 g[Q / N][N];
+#pragma unroll
+    for (int j = 0; j < Q / N; ++j) {
+#pragma unroll
+      for (int k2 = 0; k2 < N; ++k2) {
+        if constexpr (std::is_void_v<SM>) g[j][k2] = line[lam + N * j + Q * k2];
+        else g[j][k2] = pair_value<SM>(line, lam + N * j + Q * k2, r);
+      }
+      dif_stages<N, true, N / 2>(g[j]);
+    }
+    wave_lds_order();
+#pragma unroll
+    for (int j = 0; j < Q / N; ++j)
+#pragma unroll
+      for (int n1 = 0; n1 < N; ++n1) {
+        const float2 zv = g[j][brevc(n1, lgN)];
+        line[xslot<N>(lam + N * j, n1)] = n1 == 0 ? zv : cmul(zv, conjf2(twm[n1 * (lam + N * j)]));
+      }
+    wave_lds_order();
+    float2 v[Q];
+#pragma unroll
+    for (int k1 = 0; k1 < Q; ++k1) v[k1] = line[xslot<N>(k1, lam)];
+    dif_stages<Q, true, Q / 2>(v);
+    wave_lds_order();
+#pragma unroll
+    for (int n2 = 0; n2 < Q; ++n2) line[lam + N * n2] = v[brevc(n2, lgQ)];
+  }
+};
+
+// Layout of one workgroup: NZ lanes per z column, one column per lane group.
+// The half-spectrum columns of the two real planes (see YzxPairs) are placed
+// so that plane 0's fall in the first half of the wavefronts.
+template <int M, int PZ>
+struct YzHalf {
+  static constexpr int NZ = ZCol<PZ>::N, T = M * NZ, NW = T / 64, ZR = PZ / 2, RS = M + 1;
+  static constexpr int CPW = 64 / NZ, SZ = NZ < M / CPW ? NZ : M / CPW;
+  static constexpr int KC = M / 2 + 1, KPL = (PZ / 2 + 1) * KC;   // kernel slice [6][PZ/2 + 1][KC]
+  static_assert(SZ == NW || (2 * SZ == NW && SZ * CPW == M / 2), "column layout");
+  __device__ static int of(int hi, int k) {
+    if constexpr (SZ == NW) return k % (SZ / 2) + SZ * (k / (SZ / 2)) + hi * (SZ / 2);
+    else return k + hi * (M / 2);
+  }
+  __device__ static int k_of(int s) {
+    if constexpr (SZ == NW) return s % (SZ / 2) + (SZ / 2) * (s / SZ);
+    else return s & (M / 2 - 1);
+  }
+  static constexpr size_t lds(bool pair) {
+    return sizeof(float2) * ((size_t)3 * ZR * RS + M + PZ + (pair ? 6 * PZ : 0)) + sizeof(float) * 6 * (size_t)KPL;
+  }
+};
+
+// 3x3 product at column entry k2 (the slice's ky index), kz; sy: sign of the components odd in y
+template <int PZ, int KC>
+__device__ __forceinline__ void kernel_mul_half(const float* Ks, int k2, int kz, float sy, float2& mx, float2& my, float2& mz) {
+  constexpr int HZ = PZ / 2, PL = (HZ + 1) * KC;
+  const int kz2 = kz > HZ ? PZ - kz : kz;
+  const float sz = kz > HZ ? -1.f : 1.f;
+  const float* K = Ks + kz2 * KC + k2;
+  const float nxx = K[0], nyy = K[PL], nzz = K[2 * PL];
+  const float nxy = sy * K[3 * PL], nxz = sz * K[4 * PL], nyz = sy * sz * K[5 * PL];
+  const float2 a = mx, b = my, c = mz;
+  mx = make_float2(nxx * a.x + nxy * b.x + nxz * c.x, nxx * a.y + nxy * b.y + nxz * c.y);
+  my = make_float2(nxy * a.x + nyy * b.x + nyz * c.x, nxy * a.y + nyy * b.y + nyz * c.y);
+  mz = make_float2(nxz * a.x + nyz * b.x + nzz * c.x, nxz * a.y + nyz * b.y + nzz * c.y);
+}
+
+// the same in the planes kx = 0 and Px/2, from a slice [xx, yy, zz, yz][PZ/2 + 1][KC], ky <= Py/2
+template <int PZ, int KC>
+__device__ __forceinline__ void kernel_mul_real(const float* Ks, int k2, int kz, float2& mx, float2& my, float2& mz) {
+  constexpr int HZ = PZ / 2, PL = (HZ + 1) * KC;
+  const int kz2 = kz > HZ ? PZ - kz : kz;
+  const float* K = Ks + kz2 * KC + k2;
+  const float nxx = K[0], nyy = K[PL], nzz = K[2 * PL], nyz = kz > HZ ? -K[3 * PL] : K[3 * PL];
+  const float2 a = mx, b = my, c = mz;
+  mx = make_float2(nxx * a.x, nxx * a.y);
+  my = make_float2(nyy * b.x + nyz * c.x, nyy * b.y + nyz * c.y);
+  mz = make_float2(nyz * b.x + nzz * c.x, nyz * b.y + nzz * c.y);
+}
+
+template <int M, int PZ, bool PAIR>
+__device__ __forceinline__ void yzh_item(const InstDesc& D, int kx, int r, const float2* __restrict__ tw, float2* lds) {
+  using H = YzHalf<M, PZ>;
+  using YF = YFull<M>;
+  using ZC = ZCol<PZ>;
+  constexpr int NY = YF::N, NZ = H::NZ, T = H::T, NW = H::NW, ZR = H::ZR, RS = H::RS, KC = H::KC, KPL = H::KPL;
+  constexpr int RPW = 64 / NY, SY = NY / 2, HZ1 = PZ / 2 + 1, HY1 = M + 1;
+  static_assert(NW % SY == 0 && ZR % NZ == 0, "row layout");
+  float2* B = lds;
+  float2* twm = B + 3 * ZR * RS;
+  float2* twz = twm + M;
+  float* Ks = reinterpret_cast<float*>(twz + PZ);
+  float2* Pk = reinterpret_cast<float2*>(Ks + 6 * KPL);
+  load_twiddles(twm, M, tw, T);
+  load_twiddles(twz, PZ, tw, T);
+  const int ny = D.ny, nz = D.nz, nrow = 3 * nz;
+  const MMG float2* X = gbl(D.fx) + (size_t)kx * nrow * ny;
+  const MMG float2* X2 = gbl(D.fx) + (size_t)(D.kx - 1) * nrow * ny;   // PAIR: plane Px/2
+  // thread t takes column y = t mod M of rows it * NZ + t / M
+  const int y = threadIdx.x & (M - 1), r0 = threadIdx.x / M;
+  const bool yin = y < ny;
+  const int tb = r0 * ny + y;
+  // the twist W_2M^{ry} of this thread's column
+  const float2 wt = r ? tw[y * (MMI_TW_LEN / (2 * M))] : make_float2(1.f, 0.f);
+  constexpr int NX = 3 * ZR / NZ, NK = (6 * KPL + T - 1) / T;
+  // the kernel slice: entry k2 is ky = 2 k2 + r (r = 1 has one fewer; the last is not used)
+  auto kslice = [&](int plane, float (&kv)[NK]) {
+    const MMG float* K = gbl(D.kern) + (size_t)plane * 6 * HZ1 * HY1;
+#pragma unroll
+    for (int it = 0; it < NK; ++it) {
+      const int e = min(it * T + (int)threadIdx.x, 6 * KPL - 1);
+      const int row = e / KC, k2 = e - row * KC;
+      kv[it] = K[row * HY1 + min(2 * k2 + r, HY1 - 1)];
+    }
+  };
+  auto kstore = [&](const float (&kv)[NK]) {
+#pragma unroll
+    for (int it = 0; it < NK; ++it) {
+      const int e = it * T + threadIdx.x;
+      if (e < 6 * KPL) Ks[e] = kv[it];
+    }
+  };
+  // PAIR: the components xx, yy, zz, yz (xy and xz vanish in the real planes)
+  constexpr int NK4 = (4 * KPL + T - 1) / T;
+  auto kslice4 = [&](int plane, float (&kv)[NK4]) {
+    const MMG float* K = gbl(D.kern) + (size_t)plane * 6 * HZ1 * HY1;
+#pragma unroll
+    for (int it = 0; it < NK4; ++it) {
+      const int e = min(it * T + (int)threadIdx.x, 4 * KPL - 1);
+      const int row = e / KC, k2 = e - row * KC;
+      kv[it] = K[(row >= 3 * HZ1 ? row + 2 * HZ1 : row) * HY1 + min(2 * k2 + r, HY1 - 1)];
+    }
+  };
+  auto kstore4 = [&](float* dst, const float (&kv)[NK4]) {
+#pragma unroll
+    for (int it = 0; it < NK4; ++it) {
+      const int e = it * T + threadIdx.x;
+      if (e < 4 * KPL) dst[e] = kv[it];
+    }
+  };
+  float kv[PAIR ? NK4 : NK];
+  {
+    float2 xv[NX];
+#pragma unroll
+    for (int it = 0; it < NX; ++it) {
+      const int c = it * NZ / ZR, z = it * NZ % ZR + r0;
+      const bool in = yin && z < nz;
+      const int off = in ? (c * nz + it * NZ % ZR) * ny + tb : 0;
+      float2 v = gld2(X + off);
+      if constexpr (PAIR) v = make_float2(v.x, gld2(X2 + off).x);
+      xv[it] = make_float2(in ? v.x : 0.f, in ? v.y : 0.f);
+    }
+    // (in flight during the forward y pass)
+    if constexpr (PAIR) kslice4(0, kv);
+    else kslice(kx, kv);
+#pragma unroll
+    for (int it = 0; it < NX; ++it) B[(it * NZ + r0) * RS + y] = r ? cmul(xv[it], wt) : xv[it];
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int ylam = lane / RPW, yrl = lane % RPW;
+  // forward y of the rows z < nz (rows z >= nz stay zero)
+#pragma unroll 1
+  for (int g0 = wave / SY; 32 * g0 < 3 * ZR; g0 += NW / SY) {
+    const int rho = yrow_of<NY>(g0, wave, yrl);
+    if (rho < 3 * ZR && (rho & (ZR - 1)) < nz) {
+      YF::forward(B + rho * RS, ylam, twm);
+      if constexpr (PAIR) {
+        wave_lds_order();
+        YF::template split_pair<H>(B + rho * RS, ylam, r);
+      }
+    }
+  }
+  if constexpr (PAIR) kstore4(Ks, kv);
+  else kstore(kv);
+  __syncthreads();
+  // z columns, one per lane group
+  {
+    const int lam = threadIdx.x & (NZ - 1);
+    typename ZC::Tw wz;
+    ZC::twiddles(wz, twz, lam);
+    const int s = zcol_of<NZ, M>(threadIdx.x);
+    if constexpr (!PAIR) {
+      const bool up = r ? s >= M / 2 : s > M / 2;              // ky > M
+      const int k2 = up ? (r ? M - 1 - s : M - s) : s;
+      const float sy = up ? -1.f : 1.f;
+      ZC::convolve(B + s, RS, nz, lam, wz, [&](int kz, float2& a, float2& b, float2& c) {
+        kernel_mul_half<PZ, KC>(Ks, k2, kz, sy, a, b, c);
+      });
+    } else {
+      float kv2[NK4];
+      kslice4(D.kx - 1, kv2);                     // plane Px/2's kernel, in flight during the forward z
+      // columns of plane 0 in the first half of the wavefronts, of plane Px/2
+      // in the others (uniform per wavefront)
+      const bool hi = wave >= NW / 2;
+      const int k2 = H::k_of(s);
+      const bool shared = !r && k2 == 0;          // the column of ky = 0 and M
+      typename ZC::Spec sp;
+      ZC::forward(B + s, RS, lam, wz, sp);
+      // The rows are in registers now: plane Px/2's slice goes to their place,
+      // so that both halves multiply at once.
+      __syncthreads();
+      float* const Kb = reinterpret_cast<float*>(B);
+      kstore4(Kb, kv2);
+      __syncthreads();
+      const float* const Kp = hi ? Kb : Ks;
+      if (!shared)
+#pragma unroll
+        for (int j = 0; j < ZC::Q / NZ; ++j)
+#pragma unroll
+          for (int p = 0; p < NZ; ++p)
+            kernel_mul_real<PZ, KC>(Kp, k2, ZC::kz_of(lam, j, p), sp[0][j][p], sp[1][j][p], sp[2][j][p]);
+      if (!r && (wave == 0 || wave == NW / 2)) {
+        // the wavefront that holds the shared column of its plane: lane kz
+        // forms U[kz] and V[kz] from Z[kz] and Z[-kz] on a copy (see yzx_item)
+        float2* pk = Pk + (hi ? 3 * PZ : 0);
+        if (shared)
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int j = 0; j < ZC::Q / NZ; ++j)
+#pragma unroll
+              for (int p = 0; p < NZ; ++p) pk[c * PZ + ZC::kz_of(lam, j, p)] = sp[c][j][p];
+        wave_lds_order();
+        const int kz = lane & (PZ - 1), mz = (PZ - kz) & (PZ - 1);
+        float2 u[3], v[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const float2 zk = pk[c * PZ + kz], zm = pk[c * PZ + mz];
+          u[c] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+          v[c] = make_float2(0.5f * (zk.y + zm.y), 0.5f * (zm.x - zk.x));
+        }
+        wave_lds_order();                         // all of the copy read before it is overwritten
+        kernel_mul_real<PZ, KC>(Kp, 0, kz, u[0], u[1], u[2]);
+        kernel_mul_real<PZ, KC>(Kp, M / 2, kz, v[0], v[1], v[2]);
+        if (lane < PZ)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) pk[c * PZ + kz] = make_float2(u[c].x - v[c].y, u[c].y + v[c].x);
+        wave_lds_order();
+        if (shared)
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int j = 0; j < ZC::Q / NZ; ++j)
+#pragma unroll
+              for (int p = 0; p < NZ; ++p) sp[c][j][p] = pk[c * PZ + ZC::kz_of(lam, j, p)];
+      }
+      __syncthreads();
+      ZC::inverse(B + s, RS, nz, lam, wz, sp);
+    }
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int g0 = wave / SY; 32 * g0 < 3 * ZR; g0 += NW / SY) {
+    const int rho = yrow_of<NY>(g0, wave, yrl);
+    if (rho < 3 * ZR && (rho & (ZR - 1)) < nz)
+      YF::template inverse<std::conditional_t<PAIR, H, void>>(B + rho * RS, ylam, twm, r);
+  }
+  __syncthreads();
+  // this residue's term of the convolved rows
+  const size_t nX = (size_t)D.kx * nrow * ny;
+  MMG float2* O = gbl(D.fy) + (size_t)r * nX + (size_t)kx * nrow * ny;
+  MMG float2* O2 = gbl(D.fy) + (size_t)r * nX + (size_t)(D.kx - 1) * nrow * ny;
+#pragma unroll
+  for (int it = 0; it < NX; ++it) {
+    const int c = it * NZ / ZR, z = it * NZ % ZR + r0;
+    if (!yin || z >= nz) continue;
+    const int off = (c * nz + it * NZ % ZR) * ny + tb;
+    float2 v = B[(it * NZ + r0) * RS + y];
+    if (r) v = cmul(v, conjf2(wt));
+    if constexpr (PAIR) {
+      gst2(O + off, make_float2(v.x, 0.f));
+      gst2(O2 + off, make_float2(v.y, 0.f));
+    } else {
+      gst2(O + off, v);
+    }
+  }
+}
+
+// work item of an instance: 2 kx + r, kx = 0 standing for the planes 0 and Px/2
+template <int M, int PZ>
+__global__ __launch_bounds__((YzHalf<M, PZ>::T)) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_fft_yzh(const InstDesc* __restrict__ descs,
+                                                             const WorkItem* __restrict__ work,
+                                                             const float2* __restrict__ tw, int nyz, int fmethod,
+                                                             int fstage) {
+  extern __shared__ float2 lds[];
+  if ((int)blockIdx.x >= nyz) {
+    final_any(fmethod, fstage, descs, (int)blockIdx.x - nyz, reinterpret_cast<double*>(lds));
+    return;
+  }
+  // the two items of a plane on one XCD (they read the same rows)
+  const int q = nyz >> 3, rem = nyz & 7, b = blockIdx.x, xcd = b & 7;
+  const WorkItem wi = work[xcd * q + min(xcd, rem) + (b >> 3)];
+  const InstDesc& D = descs[wi.inst];
+  if (gbl(D.ctl)->done) return;
+  if (wi.item < 2) yzh_item<M, PZ, true>(D, 0, wi.item, tw, lds);
+  else yzh_item<M, PZ, false>(D, wi.item >> 1, wi.item & 1, tw, lds);
+}
+
 // ------------------------ split y passes with the same line transforms (T = 512)
 // For padded y planes too large for one workgroup's LDS: the y passes over
 // rows (kx, c, z < nz) between X[kx][c][z][y < ny] and Y[kx][c][z][ky < Py]
@@ -1437,7 +1828,6 @@ struct SplitY {
 // Workgroups nwork .. nwork + nfinal - 1 of a forward launch run the
 // finalisation of stage fstage instead (as in k_fft_yzx: the y pass reads
 // and writes only X and Y, which the finalisation does not touch).
-static_assert(MM_SX_T == MMI_WG, "the finalisation body in the extra workgroups assumes MMI_WG threads");
 template <int PY, int DIR>
 __global__ __launch_bounds__(MM_SX_T) void k_fft_ysx(const InstDesc* __restrict__ descs,
                                                     const WorkItem* __restrict__ work,
@@ -1600,8 +1990,7 @@ __global__ __launch_bounds__(MM_XR_T) void k_fft_xir(const InstDesc* __restrict_
   const int l = threadIdx.x >> 2, r = threadIdx.x & 3;
   const int ra_row = min(r0 + 2 * l, rows - 1), rb_row = min(r0 + 2 * l + 1, rows - 1);
   const bool b_in = r0 + 2 * l + 1 < rows;
-  const MMG float2* X = gbl(D.fx);
-  const size_t kstride = (size_t)rows;
+  const MMG float2* X = conv_rows(D);
   // Z[kx] = Xa[kx] + i Xb[kx] for kx <= Px/2, conj(Xa[Px-kx]) + i conj(Xb[Px-kx]) above
   float2 g[MX];
 #pragma unroll
@@ -1609,8 +1998,8 @@ __global__ __launch_bounds__(MM_XR_T) void k_fft_xir(const InstDesc* __restrict_
     const int kx = 4 * k + r;
     const bool lo = kx <= NXP;
     const int kk = lo ? kx : PX - kx;
-    float2 a = gld2(X + (size_t)kk * kstride + ra_row);
-    float2 b = gld2(X + (size_t)kk * kstride + rb_row);
+    float2 a = conv_row(D, X, kk * rows + ra_row);
+    float2 b = conv_row(D, X, kk * rows + rb_row);
     if (!b_in) b = make_float2(0.f, 0.f);
     if (kx == 0 || kx == NXP) { a.y = 0.f; b.y = 0.f; }
     g[k] = lo ? make_float2(a.x - b.y, a.y + b.x) : make_float2(a.x + b.y, b.x - a.y);
@@ -1935,6 +2324,26 @@ bool mmk_yzx_pairs(int py, int pz) {
   return (pz == 32 && mmk::YzxPairs<128, 32>::on && py == 128) || (pz == 64 && mmk::YzxPairs<64, 64>::on && py == 64);
 }
 
+#define MM_YZH_EACH(F) F(32, 32) F(64, 32) F(128, 32) F(32, 64) F(64, 64) F(128, 64)
+size_t mmk_yzh_lds(int py, int pz) {
+#define MM_YZH_LDS(A, B) \
+  if (py == 2 * A && pz == B) return mmk::YzHalf<A, B>::lds(true);
+  MM_YZH_EACH(MM_YZH_LDS)
+  return 0;
+}
+hipError_t mmk_launch_fft_yzh(int py, int pz, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
+                              const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
+#define MM_YZH_CASE(A, B)                                                                                \
+  if (py == 2 * A && pz == B) {                                                                          \
+    constexpr int T = mmk::YzHalf<A, B>::T;                                                              \
+    if (nfinal < 0 || (nfinal > 0 && lds < MMI_PSTRIDE * sizeof(double))) return hipErrorInvalidValue;   \
+    MM_LAUNCH((mmk::k_fft_yzh<A, B>), dim3(nblocks + nfinal), dim3(T), lds, s, d, w, tw,                 \
+              nblocks, fmethod, fstage);                                                                 \
+    return hipGetLastError();                                                                            \
+  }
+  MM_YZH_EACH(MM_YZH_CASE)
+  return hipErrorInvalidValue;
+}
 hipError_t mmk_launch_fft_ysx(int dir, int py, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
                               const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
   if (nfinal < 0 || (nfinal > 0 && (dir > 0 || lds < MMI_PSTRIDE * sizeof(double)))) return hipErrorInvalidValue;
@@ -1997,6 +2406,10 @@ hipError_t mmk_set_lds_limits() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   MM_YZX_ATTR(4, 8) MM_YZX_ATTR(8, 8) MM_YZX_ATTR(16, 8) MM_YZX_ATTR(32, 8)
   MM_YZX_ATTR(4, 16) MM_YZX_ATTR(8, 16) MM_YZX_ATTR(16, 16) MM_YZX_ATTR(32, 16)
+#define MM_YZH_ATTR(A, B)                                                                                  \
+  if (e == hipSuccess)                                                                                     \
+    e = hipFuncSetAttribute((const void*)mmk::k_fft_yzh<A, B>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  MM_YZH_EACH(MM_YZH_ATTR)
 #define MM_SX_ATTR(K)                                                                                      \
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   MM_SX_ATTR((mmk::k_fft_ysx<16, -1>)) MM_SX_ATTR((mmk::k_fft_ysx<32, -1>)) MM_SX_ATTR((mmk::k_fft_ysx<64, -1>))

@@ -46,6 +46,11 @@ int mmk_yzx_pad();
 // k_fft_yzx for padded (py, pz) carries the real planes kx = 0 and Px/2 of an
 // instance in one work item (item 0; no item Px/2), with 6 pz float2 more LDS
 bool mmk_yzx_pairs(int py, int pz);
+// y-z in two halves of the ky range (2 kx items per instance and the planes 0 and Px/2 in one pair of items):
+// padded y of 64..256, padded z of 32 or 64; mmk_yzh_lds is 0 for other shapes
+size_t mmk_yzh_lds(int py, int pz);
+hipError_t mmk_launch_fft_yzh(int py, int pz, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
+                              const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0, int fstage = 0);
 hipError_t mmk_launch_fft_ysx(int dir, int py, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
                               const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0,
                               int fstage = 0);

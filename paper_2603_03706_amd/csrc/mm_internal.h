@@ -113,6 +113,7 @@ struct InstDesc {
   float2* fy;                         // [Kx][3][nz][Py] (split path)
   const float* kern;                  // [Kx][6][Pz/2+1][Py/2+1]
   int px, py, pz, kx;
+  int yzh;                            // convolved rows as two terms in fy, this many elements apart (0: in place in fx)
   int xfused;                         // x passes done inside the stage kernels (see k_stage)
   // discrete adjoint (RK4): recorded segment and adjoint fields
   float* rec_m;                       // [K+1][4][S*3*cells] stage inputs of each recorded step

@@ -88,7 +88,7 @@ __device__ __forceinline__ double block_reduce(double v, double* sh) {
 // The gathers of one finalisation as one list of tasks: mode sums m^-
 // (slots MMI_SLOT_MM + 0 .. nmm-1), stage-derivative sums (MMI_SLOT_DMM +
 // 0 .. ndmm-1) and, with has_max, the NaN-propagating max of one slot over
-// the workgroups; wave w takes tasks w, w + 8, ...  Every slot is combined in
+// the workgroups; the workgroup's waves take the tasks in turn.  Every slot is combined in
 // a fixed order: lane l takes records l, l + 64, ... (eight in flight) and a
 // butterfly joins the lanes.  Results (sums times `scale`) go to tot[slot]
 // in LDS; the caller synchronises before reading them.
@@ -97,7 +97,7 @@ __device__ __forceinline__ void gather_list(const InstDesc& D, int nmm, int ndmm
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const MMG double* P = gbl(D.partials);
   const int ntask = nmm + ndmm + (has_max ? 1 : 0);
-  for (int k = wv; k < ntask; k += MMI_WG / 64) {
+  for (int k = wv; k < ntask; k += (int)blockDim.x >> 6) {
     const bool mx = has_max && k == ntask - 1;
     const int slot = mx ? max_slot : (k < nmm ? MMI_SLOT_MM + k : MMI_SLOT_DMM + (k - nmm));
     double v = 0.0;
@@ -462,8 +462,8 @@ __device__ void finalize(const InstDesc& D, InstCtl* C, const double* tot) {
   }
 }
 
-// Body of the finalisation of stage ST of instance `inst` (all MMI_WG
-// threads of the workgroup; tot: MMI_PSTRIDE doubles of LDS).
+// Body of the finalisation of stage ST of instance `inst` (all threads of
+// the workgroup, any number of whole waves; tot: MMI_PSTRIDE doubles of LDS).
 template <int METHOD, int ST>
 __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double* tot) {
   const InstDesc& D = descs[inst];

@@ -46,7 +46,7 @@ __device__ __forceinline__ XRows xrows_setup(const InstDesc& D, int lw, float2* 
 
 // demag field [T] of this thread's cell from the convolved X rows
 __device__ __forceinline__ void xrows_c2r(const InstDesc& D, const XRows& q, float (&bdv)[3]) {
-  const MMG float2* X = gbl(D.fx);
+  const MMG float2* X = conv_rows(D);
   const int half = q.Px >> 1;
   // Item (k, c, j2), k <= Px/2: the X values a, b of rows 2 j2 and 2 j2 + 1
   // give line entries Z[k] = a + i b and, by Hermitian symmetry,
@@ -57,7 +57,7 @@ __device__ __forceinline__ void xrows_c2r(const InstDesc& D, const XRows& q, flo
     const int k = rest / 3, c = rest - 3 * k;
     const int j = 2 * j2;
     const int e0 = k * q.rows + c * q.nyz + q.yz0;
-    float2 a = gld2(&gat(X, e0 + min(j, q.nrow - 1))), b = gld2(&gat(X, e0 + min(j + 1, q.nrow - 1)));
+    float2 a = conv_row(D, X, e0 + min(j, q.nrow - 1)), b = conv_row(D, X, e0 + min(j + 1, q.nrow - 1));
     if (j >= q.nrow) a = make_float2(0.f, 0.f);
     if (j + 1 >= q.nrow) b = make_float2(0.f, 0.f);
     const bool edge = k == 0 || k == half;
