@@ -128,7 +128,7 @@ void release_spectrum(Spectrum* s) {
 // --------------------------------------------------------------- layout
 struct Layout {
   size_t ctl, y[2], k[7], st[2], geom, partials, bd, fx, fy, u, fixed_end, total;
-  int ncell, nwg, S, px, py, pz, kx;
+  int ncell, nwg, cpw, S, px, py, pz, kx;
   bool fft, split;
 };
 
@@ -193,11 +193,24 @@ bool xreg_fits(int px) { return px == 16 || px == 32 || px == 64 || px == 128; }
 constexpr int XR_ROWS = 128;
 
 // x passes inside the stage kernels: a workgroup must hold at least two whole
-// x-rows of each component, so nx is a power of two from 2 to MMI_WG / 2
-bool xfuse_fits(int nx) { return nx >= 2 && nx <= MMI_WG / 2 && (nx & (nx - 1)) == 0; }
+// x-rows of each component, so nx is from 2 to MMI_WG / 2.  It takes the
+// largest power of two of rows; for other nx than powers of two up to half its
+// threads then have no cell, but the two launches and passes through memory
+// per evaluation that the separate x kernels cost are worth more: 100x60x20,
+// RK4, 143 vs 170 us per step, 200x200x1, DP45, 252 vs 286 us.
+bool xfuse_fits(int nx) { return nx >= 2 && nx <= MMI_WG / 2; }
+int xfuse_lg_rows(int nx) {
+  int lg = 0;
+  while ((2 << lg) * nx <= MMI_WG) ++lg;
+  return lg;
+}
 size_t xfuse_lds(int nx) {
-  const int R = MMI_WG / nx, J = R / 2, Px = 2 * nx;
+  const int J = (1 << xfuse_lg_rows(nx)) / 2, Px = mmh::padded(nx);
   return sizeof(float2) * ((size_t)3 * Px * (J + 1) + Px);
+}
+// cells per workgroup of the cell kernels
+int cells_per_wg(const mm_params& p) {
+  return p.demag == MM_DEMAG_FFT && p.sublattices == 1 && xfuse_fits(p.nx) ? p.nx << xfuse_lg_rows(p.nx) : MMI_WG;
 }
 const char* path_name(int p) {
   return p == PATH_REG      ? "reg"
@@ -234,7 +247,8 @@ size_t small_lds(int S, int ncell, int N) {
 Layout make_layout(const mm_params& p, int n_modes) {
   Layout L{};
   L.ncell = p.nx * p.ny * p.nz;
-  L.nwg = (L.ncell + MMI_WG - 1) / MMI_WG;
+  L.cpw = cells_per_wg(p);
+  L.nwg = (L.ncell + L.cpw - 1) / L.cpw;
   L.S = p.sublattices;
   L.fft = p.demag == MM_DEMAG_FFT;
   L.px = mmh::padded(p.nx);
@@ -516,6 +530,8 @@ mm_status upload_desc(mm_ctx* c) {
   d.lgny = lg_pow2(p.ny);
   d.S = p.sublattices; d.N = c->N; d.profiled = c->profiled ? 1 : 0; d.has_geom = p.geometry ? 1 : 0;
   d.demag = p.demag; d.method = c->method; d.nwg = L.nwg; d.wg0 = 0;
+  d.cpw = L.cpw;
+  d.lgR = L.cpw == MMI_WG && !L.fft ? 0 : xfuse_lg_rows(p.nx);
   d.split = c->split ? 1 : 0;
   const double cex = 2.0 * p.Aex / p.Ms;
   d.cex_x = p.nx > 1 ? (float)(cex / (p.dx * p.dx)) : 0.f;
@@ -2588,7 +2604,7 @@ static mm_status check_fft_x(const mm_batch* b, int32_t path) {
   for (auto& g : b->groups) {
     if (path == MM_X_REGISTER && !xreg_fits(g.px))
       return fail(MM_ERR_ARG, "register x path needs a padded x of 16..128 cells");
-    if (path == MM_X_STAGE && !g.xfused && !xfuse_fits(g.nx))
+    if (path == MM_X_STAGE && (!xfuse_fits(g.nx) || (g.nx & (g.nx - 1))))
       return fail(MM_ERR_ARG, "x passes in the stage kernels need nx a power of two from 2 to 256");
     if (path == MM_X_STAGE)
       for (int m : g.members)

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_start(const InstDesc* __restrict
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) return;
   const int nc = D.ncell, S = D.S;
-  const int i = (lblk - D.wg0) * MMI_WG + threadIdx.x;
+  const int i = wg_cell(D, lblk - D.wg0);
   if (i >= nc) return;
   const bool mag = !D.has_geom || gbl(D.geom)[i];
   const size_t vec = (size_t)3 * S * nc;
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_a(const InstDesc* __restrict__ d
   if (C->done) return;
   const int lw = lblk - D.wg0;
   const int nc = D.ncell, S = D.S, N = D.N;
-  const int i = lw * MMI_WG + threadIdx.x;
+  const int i = wg_cell(D, lw);
   const bool valid = i < nc;
   const bool mag = valid && (!D.has_geom || gbl(D.geom)[i]);
   const int ri = C->rec_index;
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_b(const InstDesc* __restrict__ d
     load_twiddles(xq.twl, xq.Px, tw, MMI_WG);
     xrows_c2r(D, xq, bdv);
   }
-  const int i = lw * MMI_WG + threadIdx.x;
+  const int i = wg_cell(D, lw);
   if (i >= nc) return;   // no barrier below
   const bool mag = !D.has_geom || gbl(D.geom)[i];
   const int nx = D.nx, ny = D.ny, nz = D.nz;

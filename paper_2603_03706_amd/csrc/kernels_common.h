@@ -243,8 +243,8 @@ __device__ __forceinline__ int xcd_block() {
   return x * q + min(x, r) + (b >> 3);
 }
 
-// Workgroup (of MMI_WG cells) that the lw-th workgroup of an instance takes.
-// Where a z-plane is a whole number P >= 64 of workgroups, consecutive
+// Workgroup (of D.cpw cells) that the lw-th workgroup of an instance takes.
+// Where a z-plane is a whole number P >= 64 of full workgroups, consecutive
 // workgroups walk z first (lw = b nz + z takes block b of plane z), so that
 // the planes a stencil reads above and below are fetched by workgroups that
 // run close together on the same XCD (otherwise P workgroups apart, about
@@ -253,9 +253,16 @@ __device__ __forceinline__ int xcd_block() {
 // workgroups; the workgroup's cells, x-rows and partial record follow it.
 __device__ __forceinline__ int zmajor_wg(const InstDesc& D, int lw) {
   const int plane = D.nx * D.ny;
-  if ((plane & (MMI_WG - 1)) || plane < 64 * MMI_WG) return lw;
+  if (D.cpw != MMI_WG || (plane & (MMI_WG - 1)) || plane < 64 * MMI_WG) return lw;
   const int P = plane >> MMI_LG_WG, b = lw / D.nz;
   return (lw - b * D.nz) * P + b;
+}
+
+// Cell of this thread in workgroup lw of the instance, or ncell (no cell):
+// every thread of a workgroup has one, except where the workgroup holds whole
+// x-rows that leave some threads over (D.cpw < MMI_WG).
+__device__ __forceinline__ int wg_cell(const InstDesc& D, int lw) {
+  return (int)threadIdx.x < D.cpw ? lw * D.cpw + (int)threadIdx.x : D.ncell;
 }
 
 // Coordinates of cell i = (z ny + y) nx + x: shifts and masks when nx and ny

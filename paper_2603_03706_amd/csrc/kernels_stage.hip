@@ -89,8 +89,12 @@ __device__ __forceinline__ void reduce_modes(const InstDesc& D, int i, bool mag,
 // --------------------------------------------------------------- the kernel
 // METHOD RK4: ST = 0 run start (reductions only), 1..4 stages.
 // METHOD DP45: ST = 1 run start (k1), 2..7 stages.
+// At most 80 scalar registers: allocated in sixteens with sixteen more for the
+// trap handler, 82 leave seven wavefronts per SIMD, and workgroups of eight
+// wavefronts then run three to a CU instead of four (stage 5 of the sweep
+// 72.6 vs 64.5 us, stage 6 74.8 vs 65.2 us with 82).
 template <int METHOD, int ST>
-__global__ __launch_bounds__(MMI_WG) void k_stage(const InstDesc* __restrict__ descs,
+__global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k_stage(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
                                                   const float2* __restrict__ tw) {
   __shared__ double sh[MODE_CHUNK * 2 * (MMI_WG / 64)];
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(MMI_WG) void k_stage(const InstDesc* __restrict__ d
   if (C->done) return;
   const int lw = zmajor_wg(D, lblk - D.wg0);
   const int nc = D.ncell;
-  const int i = lw * MMI_WG + threadIdx.x;
+  const int i = wg_cell(D, lw);
   const bool valid = i < nc;
   const bool mag = valid && (!D.has_geom || gat(gbl(D.geom), i));
   const int cur = C->cur;
@@ -410,7 +414,7 @@ hipError_t mmk_launch_stage(int method, int stage, bool final_pass, int nblocks,
 namespace mmk {
 // x-forward pass of a stage input that no stage kernel produced (the DP45
 // stage-2 input y + h a21 k1, the run-start state), for the instances whose
-// x passes run inside the stage kernels: each MMI_WG-cell workgroup of the
+// x passes run inside the stage kernels: each workgroup of the
 // stage grid forms its cells' input and writes the X rows of its own x-rows
 // with the stage kernels' R2C.  Other instances return at once.
 __global__ __launch_bounds__(MMI_WG) void k_xfwd_cells(const InstDesc* __restrict__ descs,
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(MMI_WG) void k_xfwd_cells(const InstDesc* __restric
   if (C->done || !D.xfused) return;
   const int lw = lblk - D.wg0;
   const int nc = D.ncell;
-  const int i = lw * MMI_WG + threadIdx.x;
+  const int i = wg_cell(D, lw);
   const Src src = stage_src(D, C, method, stage);
   const XRows xq = xrows_setup(D, lw, xl);
   load_twiddles(xq.twl, xq.Px, tw, MMI_WG);

@@ -69,6 +69,7 @@ struct InstDesc {
   int lgnx, lgny;                     // log2 of nx, ny when powers of two, else -1
   int S, N, profiled, has_geom;
   int demag, method, nwg, wg0;
+  int cpw, lgR;                       // cells per workgroup of the cell kernels; log2 of its x-rows (FFT demag)
   int split;                          // RK4 in the operator-split scheme (cavity first, m^- held)
   int small;                          // steps run in k_small_rk4: the per-stage kernels skip the instance
   int small_u, pad_small;             // k_small_rk4 keeps the mode profiles in LDS
