@@ -303,10 +303,10 @@ mm_status mm_batch_tune(mm_batch* b, char* report, size_t report_len);
 mm_status mm_batch_tune_fft(mm_batch* b, char* report, size_t report_len);
 
 /* Demag y-z strategy for every FFT grid shape in the batch (mm_batch_tune
- * chooses one per shape by timing; before that the exchange strategy is used
- * where it applies, else the halved one, else the eight-lane register one, else the register one,
- * else the fused one where it fits, else the split exchange one, else the
- * split one):
+ * chooses one per shape by timing; before that the shape alone decides: the
+ * halved strategy for padded y of 256 and for 128 x 64, else the first of
+ * exchange, short, eight-lane register, register and fused that applies, else
+ * the split exchange one, else the split one):
  *   MM_YZ_FUSED     y and z lines transformed in LDS by one workgroup per
  *                   (instance, kx), z in tiles of ky columns;
  *   MM_YZ_REGISTER  one workgroup per (instance, kx), each line split over
@@ -325,6 +325,10 @@ mm_status mm_batch_tune_fft(mm_batch* b, char* report, size_t report_len);
  *                   the row and column transforms of MM_YZ_EXCHANGE on half
  *                   the ky range; padded y of 64..256, padded z of 32 or 64,
  *                   nx >= 2.
+ *   MM_YZ_SHORT     one workgroup per (instance, kx) with the lanes that a few
+ *                   z planes need, lines as in MM_YZ_EXCHANGE; padded z of
+ *                   4..16 with padded y of 8..256, or one z plane with padded
+ *                   y of 8..512.
  * All of them compute the same convolution (agreement to FP32 rounding).
  * Returns MM_ERR_ARG, changing nothing, if some shape cannot use `path`. */
 enum {
@@ -334,7 +338,8 @@ enum {
   MM_YZ_REGISTER8 = 3,
   MM_YZ_EXCHANGE = 4,
   MM_YZ_SPLIT_EXCHANGE = 5,
-  MM_YZ_HALVES = 6
+  MM_YZ_HALVES = 6,
+  MM_YZ_SHORT = 7
 };
 mm_status mm_batch_set_fft_path(mm_batch* b, int32_t path);
 

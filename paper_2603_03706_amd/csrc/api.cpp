@@ -167,7 +167,8 @@ enum {
   PATH_REG8 = MM_YZ_REGISTER8,
   PATH_XCH = MM_YZ_EXCHANGE,
   PATH_SPLITX = MM_YZ_SPLIT_EXCHANGE,
-  PATH_HALVES = MM_YZ_HALVES
+  PATH_HALVES = MM_YZ_HALVES,
+  PATH_SHORT = MM_YZ_SHORT
 };
 // eight lanes per z column: padded z of 32 or 64
 bool reg8_fits(int ny, int nz, int py, int pz) { return reg_fits(ny, nz, py, pz) && (pz == 32 || pz == 64); }
@@ -182,6 +183,8 @@ bool splitx_fits(int py) { return mmk_sx_rows(py) > 0; }
 size_t splitx_lds_y(int py) { return sizeof(float2) * ((size_t)mmk_sx_rows(py) * (py + 1) + py); }
 // two halves of the ky range per plane: padded y of 64..256, padded z of 32 or 64, at least three kx planes
 bool halves_fits(int py, int pz, int kx) { return kx >= 3 && mmk_yzh_lds(py, pz) > 0; }
+// few z planes: padded z of 1, 4, 8 or 16
+bool short_fits(int py, int pz) { return mmk_yzs_lds(py, pz) > 0; }
 bool xch_fits(int ny, int nz, int py, int pz) {
   (void)ny, (void)nz;
   const bool y_ok = py == 16 || py == 32 || py == 64 || py == 128;
@@ -219,6 +222,7 @@ const char* path_name(int p) {
          : p == PATH_SPLIT  ? "split"
          : p == PATH_SPLITX ? "splitx"
          : p == PATH_HALVES ? "halves"
+         : p == PATH_SHORT  ? "short"
                             : "fused";
 }
 
@@ -714,11 +718,15 @@ mm_status build_group(mm_batch::Group& g, DevArena* arena = nullptr) {
   g.lds_xf = g.Wx == 0 ? 0 : sizeof(float2) * ((size_t)g.px * (g.Wx + 1) + g.px);
   g.lds_xi = g.Wx == 0 ? 0 : sizeof(float2) * ((size_t)g.px * (g.Wx + 1) + (size_t)g.kx * 2 * g.Wx + g.px);
   g.lds_yz = halves                                         ? mmk_yzh_lds(g.py, g.pz)
+             : g.path == PATH_SHORT                         ? mmk_yzs_lds(g.py, g.pz)
              : g.path == PATH_XCH                           ? xch_lds(g.py, g.pz)
              : (g.path == PATH_REG || g.path == PATH_REG8) ? reg_lds(g.nz, g.py, g.pz)
                                                            : fused_lds(g.ny, g.nz, g.py, g.pz, g.TK);
   g.lds_y = sx ? splitx_lds_y(g.py) : sizeof(float2) * ((size_t)g.py * (g.Wy + 1) + g.py);
   g.lds_zc = sizeof(float2) * ((size_t)g.pz * 3 * g.TW + g.pz);
+  // (room for the sums of a finalisation riding on the launch)
+  g.lds_yz = std::max(g.lds_yz, sizeof(double) * MMI_PSTRIDE);
+  g.lds_y = std::max(g.lds_y, sizeof(double) * MMI_PSTRIDE);
   return MM_OK;
 }
 
@@ -848,12 +856,14 @@ mm_status batch_build(mm_batch* b, DevArena* arena = nullptr) {
       g = &b->groups.back();
       g->nx = c->p.nx; g->ny = c->p.ny; g->nz = c->p.nz;
       g->px = c->L.px; g->py = c->L.py; g->pz = c->L.pz; g->kx = c->L.kx;
-      // The exchange kernel holds a whole plane; where that fills a CU's LDS
+      // Few z planes: the short kernels (see there for both sides' times).
+      // Else the exchange kernel, which holds a whole plane; where that fills a CU's LDS
       // (128 x 64) or exceeds it (256 x 64), halves are the faster, and 256 x 32
       // goes with them.  us per launch: 101 planes' worth of 100x60x20 16.4 vs
       // 18.9, the 128x128x32 film 28.6 vs 53.7 in split passes.
       g->path = halves_fits(g->py, g->pz, g->kx) && (g->py == 256 || (g->py == 128 && g->pz == 64)) ? PATH_HALVES
                 : xch_fits(g->ny, g->nz, g->py, g->pz)  ? PATH_XCH
+                : short_fits(g->py, g->pz)              ? PATH_SHORT
                 : reg8_fits(g->ny, g->nz, g->py, g->pz) ? PATH_REG8
                 : reg_fits(g->ny, g->nz, g->py, g->pz)  ? PATH_REG
                 : c->L.split && splitx_fits(g->py)     ? PATH_SPLITX
@@ -961,9 +971,10 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
           return mmk_launch_fft_xf(g.Wx, g.n_xf, g.lds_xf, b->d_desc, g.xf, method, stage, g_twiddle, b->stream);
         }))
       return s;
-    if (g.path == PATH_HALVES) {
+    if (g.path == PATH_HALVES || g.path == PATH_SHORT) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
-            return mmk_launch_fft_yzh(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
+            auto f = g.path == PATH_HALVES ? mmk_launch_fft_yzh : mmk_launch_fft_yzs;
+            return f(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
                                       first ? nfinal : 0, b->method, final_st);
           }))
         return s;
@@ -976,12 +987,14 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
         return s;
     } else if (g.path == PATH_REG) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
-            return mmk_launch_fft_yzr(g.py / 4, g.pz / 4, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream);
+            return mmk_launch_fft_yzr(g.py / 4, g.pz / 4, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
+                                      first ? nfinal : 0, b->method, final_st);
           }))
         return s;
     } else if (g.path == PATH_FUSED) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
-            return mmk_launch_fft_yz(g.TK, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream);
+            return mmk_launch_fft_yz(g.TK, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
+                                     first ? nfinal : 0, b->method, final_st);
           }))
         return s;
     } else if (g.path == PATH_SPLITX) {
@@ -1000,7 +1013,8 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
         return s;
     } else {
       if (mm_status s = launch(b, "fft_y_forward", [&] {
-            return mmk_launch_fft_y(-1, g.Wy, g.n_y, g.lds_y, b->d_desc, g.y, g_twiddle, b->stream);
+            return mmk_launch_fft_y(-1, g.Wy, g.n_y, g.lds_y, b->d_desc, g.y, g_twiddle, b->stream,
+                                    first ? nfinal : 0, b->method, final_st);
           }))
         return s;
       if (mm_status s = launch(b, "fft_z_convolve", [&] {
@@ -1096,16 +1110,12 @@ mm_status enqueue_start(mm_batch* b) {
 // One step.  Where the stage kernels do the x passes, each stage's input is
 // already in X (written by the previous stage kernel) except the DP45 stage
 // 2 input, which depends on the step size chosen after stage 7.
-// The finalisation of a stage other than the last of the step runs as extra
-// workgroups of the next stage's first y-z launch when that launch is the
-// eight-lane, the two-pass or the split two-pass y forward kernel: the
-// transform reads and writes only X (and Y), which the finalisation does not
-// touch, and the next stage kernel comes after both in stream order.
-bool merge_final(const mm_batch* b) {
-  if (b->groups.empty()) return false;
-  const int p = b->groups[0].path;
-  return p == PATH_REG8 || p == PATH_XCH || p == PATH_HALVES || p == PATH_SPLITX;
-}
+// With FFT demag, the finalisation of a stage other than the last of the step
+// runs as extra workgroups of the next stage's first y-z (or y-forward)
+// launch: the transform reads and writes only X (and Y), which the
+// finalisation does not touch, and the next stage kernel comes after both in
+// stream order.
+bool merge_final(const mm_batch* b) { return !b->groups.empty(); }
 
 mm_status enqueue_step(mm_batch* b) {
   if (!b->gen_wg) return MM_OK;
@@ -2557,7 +2567,7 @@ mm_status mm_batch_end(mm_batch* b) {
 
 static mm_status check_fft_path(const mm_batch* b, int32_t path) {
   if (path != PATH_FUSED && path != PATH_REG && path != PATH_SPLIT && path != PATH_REG8 && path != PATH_XCH &&
-      path != PATH_SPLITX && path != PATH_HALVES)
+      path != PATH_SPLITX && path != PATH_HALVES && path != PATH_SHORT)
     return fail(MM_ERR_ARG, "unknown y-z path");
   for (const mm_batch* p : b->parts)
     if (mm_status s = check_fft_path(p, path)) return s;
@@ -2570,6 +2580,8 @@ static mm_status check_fft_path(const mm_batch* b, int32_t path) {
       return fail(MM_ERR_ARG, "split exchange y-z path needs padded y in 16..256");
     if (path == PATH_XCH && !xch_fits(g.ny, g.nz, g.py, g.pz))
       return fail(MM_ERR_ARG, "exchange y-z path needs padded y in 16..128 and padded z of 32 or 64");
+    if (path == PATH_SHORT && !short_fits(g.py, g.pz))
+      return fail(MM_ERR_ARG, "short-z path needs padded z of 4..16 with padded y of 8..256, or one z plane with padded y of 8..512");
     if (path == PATH_HALVES && !halves_fits(g.py, g.pz, g.kx))
       return fail(MM_ERR_ARG, "halved y-z path needs padded y in 64..256, padded z of 32 or 64 and two or more cells along x");
     if (path == PATH_FUSED && !fused_fits(g.ny, g.nz, g.py, g.pz))
@@ -2923,6 +2935,17 @@ static mm_status tune_fft(mm_batch* b, std::string& out) {
         return s;
       yrep += (yrep.empty() ? "" : ", ") + std::string("\"xch\": ") + std::to_string(us);
       if (us < bestYZ) { bestYZ = us; bestPath = PATH_XCH; }
+    }
+    if (short_fits(g.py, g.pz)) {
+      g.path = PATH_SHORT;
+      if (mm_status s = build_group(g)) return s;
+      double us;
+      if (mm_status s = timed([&] {
+            return mmk_launch_fft_yzs(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream);
+          }, &us))
+        return s;
+      yrep += (yrep.empty() ? "" : ", ") + std::string("\"short\": ") + std::to_string(us);
+      if (us < bestYZ) { bestYZ = us; bestPath = PATH_SHORT; }
     }
     if (halves_fits(g.py, g.pz, g.kx)) {
       g.path = PATH_HALVES;

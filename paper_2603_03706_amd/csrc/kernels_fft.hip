@@ -18,9 +18,11 @@
 // pass is needed between them.
 #include <type_traits>
 #include "mm_internal.h"
+#include "mm_host.h"
 #include "kernels_common.h"
 #include "launch.h"
 #include "fft_lds.h"
+#include "fft_lines.h"
 #include "stage_final.h"
 
 namespace mmk {
@@ -38,23 +40,6 @@ __device__ __forceinline__ void kernel_mul(const InstDesc& D, int kx, int ky, in
   const MMG float* K = gbl(D.kern) + (size_t)kx * 6 * plane;
   const float nxx = K[o], nyy = K[plane + o], nzz = K[2 * plane + o];
   const float nxy = sy * K[3 * plane + o], nxz = sz * K[4 * plane + o], nyz = sy * sz * K[5 * plane + o];
-  const float2 a = mx, b = my, c = mz;
-  mx = make_float2(nxx * a.x + nxy * b.x + nxz * c.x, nxx * a.y + nxy * b.y + nxz * c.y);
-  my = make_float2(nxy * a.x + nyy * b.x + nyz * c.x, nxy * a.y + nyy * b.y + nyz * c.y);
-  mz = make_float2(nxz * a.x + nyz * b.x + nzz * c.x, nxz * a.y + nyz * b.y + nzz * c.y);
-}
-
-// the same multiply with the kernel slice of one kx staged in LDS as [6][PZ/2+1][PY/2+1]
-template <int PY, int PZ>
-__device__ __forceinline__ void kernel_mul_lds(const float* Ks, int ky, int kz, float2& mx, float2& my, float2& mz) {
-  constexpr int HY = PY / 2, HZ = PZ / 2, PL = (HZ + 1) * (HY + 1);
-  int ky2 = ky, kz2 = kz;
-  float sy = 1.f, sz = 1.f;
-  if (ky > HY) { ky2 = PY - ky; sy = -1.f; }
-  if (kz > HZ) { kz2 = PZ - kz; sz = -1.f; }
-  const float* K = Ks + kz2 * (HY + 1) + ky2;
-  const float nxx = K[0], nyy = K[PL], nzz = K[2 * PL];
-  const float nxy = sy * K[3 * PL], nxz = sz * K[4 * PL], nyz = sy * sz * K[5 * PL];
   const float2 a = mx, b = my, c = mz;
   mx = make_float2(nxx * a.x + nxy * b.x + nxz * c.x, nxx * a.y + nxy * b.y + nxz * c.y);
   my = make_float2(nxy * a.x + nyy * b.x + nyz * c.x, nxy * a.y + nyy * b.y + nyz * c.y);
@@ -234,8 +219,13 @@ __global__ __launch_bounds__(256) void k_fft_xi(const InstDesc* __restrict__ des
 #define MM_YZ_T 512
 __global__ __launch_bounds__(MM_YZ_T) void k_fft_yz(const InstDesc* __restrict__ descs,
                                                     const WorkItem* __restrict__ work,
-                                                    const float2* __restrict__ tw, int TK) {
+                                                    const float2* __restrict__ tw, int TK, int nwork, int fmethod,
+                                                    int fstage) {
   extern __shared__ float2 lds[];
+  if ((int)blockIdx.x >= nwork) {
+    final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
+    return;
+  }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
   if (gbl(D.ctl)->done) return;
@@ -328,38 +318,6 @@ __global__ __launch_bounds__(MM_YZ_T) void k_fft_yz(const InstDesc* __restrict__
 // so only the three phase changes need workgroup barriers.
 #define MM_YZR_T 256
 
-__host__ __device__ constexpr int brevc(int p, int lg) {
-  int r = 0;
-  for (int b = 0; b < lg; ++b) r |= ((p >> b) & 1) << (lg - 1 - b);
-  return r;
-}
-__host__ __device__ constexpr int ilog2c(int m) { return m <= 1 ? 0 : 1 + ilog2c(m >> 1); }
-
-// cos(2 pi j / 16)
-__device__ __forceinline__ constexpr float cos16(int j) {
-  j &= 15;
-  switch (j) {
-    case 0: return 1.0f;
-    case 1: case 15: return 0.92387953251128674f;
-    case 2: case 14: return 0.70710678118654752f;
-    case 3: case 13: return 0.38268343236508977f;
-    case 4: case 12: return 0.0f;
-    case 5: case 11: return -0.38268343236508977f;
-    case 6: case 10: return -0.70710678118654752f;
-    case 7: case 9: return -0.92387953251128674f;
-    default: return -1.0f;
-  }
-}
-
-// d * W_M^{k} (forward, W_M = e^{-2 pi i / M}) or d * W_M^{-k} (inverse), 0 <= k < M/2, M <= 16
-template <int M, bool INV>
-__device__ __forceinline__ float2 twc(float2 d, int k) {
-  if (k == 0) return d;
-  const int j = k * (16 / M);
-  if (j == 4) return rot<INV>(d);
-  const float c = cos16(j), sn = INV ? cos16(j - 4) : -cos16(j - 4);
-  return make_float2(d.x * c - d.y * sn, d.x * sn + d.y * c);
-}
 // d * W_M^{+-k} for M = 32 (angles on the 32-point circle)
 template <bool INV>
 __device__ __forceinline__ float2 twc32(float2 d, int k, const float2* tw32) {
@@ -457,12 +415,17 @@ __device__ __forceinline__ float2 fold_c(float2 x0, float2 x1, Root4 c, float2 w
 template <int MY, int MZ>
 __global__ __launch_bounds__(MM_YZR_T, 2) void k_fft_yzr(const InstDesc* __restrict__ descs,
                                                          const WorkItem* __restrict__ work,
-                                                         const float2* __restrict__ tw) {
+                                                         const float2* __restrict__ tw, int nwork, int fmethod,
+                                                         int fstage) {
   // LDS rows [3][2 MZ][RS]: row (c, z) holds y samples, zero beyond (nz, ny),
   // so every line read below is unconditional with compile-time offsets
   constexpr int PY = 4 * MY, PZ = 4 * MZ, RS = PY + 1, ZR = 2 * MZ, YR = 2 * MY;
   constexpr int lgMY = ilog2c(MY), lgMZ = ilog2c(MZ), lgPY = lgMY + 2;
   extern __shared__ float2 lds[];
+  if ((int)blockIdx.x >= nwork) {
+    final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
+    return;
+  }
   float2* B = lds;
   float2* twy = B + 3 * ZR * RS;
   float2* twz = twy + PY;
@@ -863,295 +826,6 @@ __global__ __launch_bounds__(MM_YZ8_T) __attribute__((amdgpu_waves_per_eu(4, 4))
 //   inverse z (in place);  inverse y per row (in place);  store X.
 #define MM_YZX_T 512
 
-// points per lane Q and lanes per line L of a padded length P (Q >= L):
-// y rows take up to sixteen points per lane, z columns eight
-template <int P, int QMAX>
-struct LinePass {
-  static constexpr int Q = P / 2 < QMAX ? P / 2 : QMAX, L = P / Q;
-  static constexpr int lgQ = ilog2c(Q), lgL = ilog2c(L);
-  static_assert(Q >= L && L >= 2, "unsupported padded length");
-};
-
-// radix-2 DIF stages h = H0 .. 1 of an in-register M-point DFT (M <= 16):
-// natural order in, bit-reversed out when H0 = M/2
-template <int M, bool INV, int H0>
-__device__ __forceinline__ void dif_stages(float2 (&v)[M]) {
-#pragma unroll
-  for (int h = H0; h >= 1; h >>= 1) {
-#pragma unroll
-    for (int g = 0; g < M; g += 2 * h) {
-#pragma unroll
-      for (int i = 0; i < h; ++i) {
-        const float2 a = v[g + i], b = v[g + i + h];
-        v[g + i] = cadd(a, b);
-        v[g + i + h] = twc<M, INV>(csub(a, b), i * (M / (2 * h)));
-      }
-    }
-  }
-}
-// the same DFT of a sequence whose entries M/2 .. M-1 are zero (not read):
-// the first stage has nothing to add and only scales
-template <int M, bool INV>
-__device__ __forceinline__ void dif_half(float2 (&v)[M]) {
-#pragma unroll
-  for (int i = 0; i < M / 2; ++i) v[i + M / 2] = twc<M, INV>(v[i], i);
-  if constexpr (M >= 4) dif_stages<M, INV, M / 4>(v);
-}
-
-// exchange slot of value k1 from / for lane a: groups of L slots, rotated by
-// k1 so that a write of fixed k1 and a read of fixed a both spread over L
-// groups (and so over LDS banks)
-template <int L>
-__device__ __forceinline__ int xslot(int k1, int a) {
-  return k1 * L + ((a + k1) & (L - 1));
-}
-
-// order the wavefront's LDS accesses across lanes (no instruction: a
-// wavefront's LDS operations already complete in issue order)
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
-
-// The y transforms of one row held in LDS by N lanes (lane lam).  Forward:
-// inputs at slots [0, P/2), afterwards slot k holds X[k].  Inverse: slot k
-// holds X[k], afterwards slots [0, P/2) hold the inverse transform (no 1/P).
-// wf[k1] = W_P^{lam k1}; wv[j][n1] = W_P^{-n1 (lam + N j)}.
-template <int P>
-struct YRow {
-  using LP = LinePass<P, 16>;
-  static constexpr int Q = LP::Q, N = LP::L;
-  struct Tw {
-    float2 wf[Q], wv[Q / N][N];
-  };
-  __device__ static void twiddles(Tw& w, const float2* tw, int lam) {
-#pragma unroll
-    for (int k1 = 0; k1 < Q; ++k1) w.wf[k1] = tw[lam * k1];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int n1 = 0; n1 < N; ++n1) w.wv[j][n1] = conjf2(j == 0 ? w.wf[n1] : tw[n1 * (lam + N * j)]);
-  }
-  __device__ static void forward(float2* line, int lam, const Tw& w) {
-    float2 v[Q];
-#pragma unroll
-    for (int n1 = 0; n1 < Q / 2; ++n1) v[n1] = line[N * n1 + lam];
-    dif_half<Q, false>(v);
-    wave_lds_order();
-#pragma unroll
-    for (int p = 0; p < Q; ++p) {
-      const int k1 = brevc(p, LP::lgQ);
-      line[xslot<N>(k1, lam)] = k1 ? cmul(v[p], w.wf[k1]) : v[p];
-    }
-    wave_lds_order();
-    float2 u[Q / N][N];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j) {
-#pragma unroll
-      for (int a = 0; a < N; ++a) u[j][a] = line[xslot<N>(lam + N * j, a)];
-      dif_stages<N, false, N / 2>(u[j]);
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int p = 0; p < N; ++p) line[lam + N * j + Q * brevc(p, LP::lgL)] = u[j][p];
-  }
-  // Two real rows A, B transformed as one row A + iB: afterwards slot
-  // SM::of(0, k) holds A[k] = (X[k] + conj X[P-k]) / 2 and SM::of(1, k) holds
-  // B[k] = (X[k] - conj X[P-k]) / 2i for k < P/2, except that the real values
-  // at k = 0 and P/2 share the slots of k = 0: (A[0], A[P/2]) and (B[0], B[P/2]).
-  template <class SM>
-  __device__ static void split_pair(float2* line, int lam) {
-    constexpr int H = P / 2, NI = H / N;
-    float2 r[NI], q[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lam + N * i;
-      r[i] = line[k];
-      q[i] = line[k == 0 ? H : P - k];
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lam + N * i;
-      const bool z = k == 0;
-      line[SM::of(0, k)] = z ? make_float2(r[i].x, q[i].x) : make_float2(0.5f * (r[i].x + q[i].x), 0.5f * (r[i].y - q[i].y));
-      line[SM::of(1, k)] = z ? make_float2(r[i].y, q[i].y) : make_float2(0.5f * (r[i].y + q[i].y), 0.5f * (q[i].x - r[i].x));
-    }
-  }
-  // The inverse's input at k = k1 + Q k2 from two half spectra laid out as
-  // split_pair leaves them (both of real rows, so X[P-k] = conj X[k]):
-  // A[k] + i B[k], whose inverse has A's row as real and B's as imaginary part.
-  template <class SM>
-  __device__ static float2 pair_value(const float2* line, int k1, int k2) {
-    constexpr int H = P / 2;
-    if (k2 < N / 2) {                            // k < P/2
-      const int k = k1 + Q * k2;
-      const float2 a = line[SM::of(0, k)], b = line[SM::of(1, k)];
-      return k == 0 ? make_float2(a.x, b.x) : make_float2(a.x - b.y, a.y + b.x);
-    }
-    const int m = P - (k1 + Q * k2);             // 1 .. P/2
-    const int i = m == H ? 0 : m;
-    const float2 a = line[SM::of(0, i)], b = line[SM::of(1, i)];
-    return m == H ? make_float2(a.y, b.y) : make_float2(a.x + b.y, b.x - a.y);
-  }
-  // SM = void: a plain row; else two half spectra (split_pair's layout)
-  template <class SM = void>
-  __device__ static void inverse(float2* line, int lam, const Tw& w) {
-    float2 g[Q / N][N];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j) {
-#pragma unroll
-      for (int k2 = 0; k2 < N; ++k2) {
-        if constexpr (std::is_void_v<SM>) g[j][k2] = line[lam + N * j + Q * k2];
-        else g[j][k2] = pair_value<SM>(line, lam + N * j, k2);
-      }
-      dif_stages<N, true, N / 2>(g[j]);
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int n1 = 0; n1 < N; ++n1) {
-        const float2 zv = g[j][brevc(n1, LP::lgL)];
-        line[xslot<N>(lam + N * j, n1)] = n1 == 0 ? zv : cmul(zv, w.wv[j][n1]);
-      }
-    wave_lds_order();
-    float2 v[Q];
-#pragma unroll
-    for (int k1 = 0; k1 < Q; ++k1) v[k1] = line[xslot<N>(k1, lam)];
-    dif_stages<Q, true, Q / 2>(v);
-    wave_lds_order();
-#pragma unroll
-    for (int n2 = 0; n2 < Q / 2; ++n2) line[lam + N * n2] = v[brevc(n2, LP::lgQ)];
-  }
-};
-
-// The z convolution of one column held in LDS by N lanes (lane lam): the
-// three components at rows c ZR + z (stride RS, ZR = P/2; rows nz .. ZR-1
-// zero), forward z, the kernel multiply kmul(kz, x, y, z) at every kz, the
-// inverse z; rows z < nz receive the result.  The column's 3 ZR slots serve
-// as the exchange area once its inputs are in registers.
-template <int P>
-struct ZCol {
-  using LP = LinePass<P, 8>;
-  static constexpr int Q = LP::Q, N = LP::L, ZR = P / 2;
-  struct Tw {
-    float2 wf[Q], wv[Q / N][N];
-  };
-  __device__ static void twiddles(Tw& w, const float2* tw, int lam) {
-#pragma unroll
-    for (int k1 = 0; k1 < Q; ++k1) w.wf[k1] = tw[lam * k1];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int n1 = 0; n1 < N; ++n1) w.wv[j][n1] = conjf2(j == 0 ? w.wf[n1] : tw[n1 * (lam + N * j)]);
-  }
-  using Spec = float2[3][Q / N][N];
-  // frequency of sp[c][j][p] after forward(): k1 + Q brev(p), k1 = lam + N j
-  __device__ static int kz_of(int lam, int j, int p) { return lam + N * j + Q * brevc(p, LP::lgL); }
-  __device__ static void forward(float2* col, int RS, int lam, const Tw& w, Spec& sp) {
-    float2 xin[3][Q / 2];
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-      for (int n1 = 0; n1 < Q / 2; ++n1) xin[c][n1] = col[(c * ZR + N * n1 + lam) * RS];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      float2 v[Q];
-#pragma unroll
-      for (int n1 = 0; n1 < Q / 2; ++n1) v[n1] = xin[c][n1];
-      dif_half<Q, false>(v);
-      wave_lds_order();
-#pragma unroll
-      for (int p = 0; p < Q; ++p) {
-        const int k1 = brevc(p, LP::lgQ);
-        col[xslot<N>(k1, lam) * RS] = k1 ? cmul(v[p], w.wf[k1]) : v[p];
-      }
-      wave_lds_order();
-#pragma unroll
-      for (int j = 0; j < Q / N; ++j) {
-#pragma unroll
-        for (int a = 0; a < N; ++a) sp[c][j][a] = col[xslot<N>(lam + N * j, a) * RS];
-        dif_stages<N, false, N / 2>(sp[c][j]);
-      }
-      wave_lds_order();
-    }
-  }
-  // inverse z of sp (the column's slots are the exchange area); rows z < nz
-  // receive the result
-  __device__ static void inverse(float2* col, int RS, int nz, int lam, const Tw& w, Spec& sp) {
-    float2 res[3][Q / 2];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-      for (int j = 0; j < Q / N; ++j) {
-        float2 g[N];
-#pragma unroll
-        for (int k2 = 0; k2 < N; ++k2) g[k2] = sp[c][j][brevc(k2, LP::lgL)];
-        dif_stages<N, true, N / 2>(g);
-        // g[p] = sum_k2 X[k1 + Q k2] W_N^{-n1 k2} at n1 = brev(p)
-#pragma unroll
-        for (int n1 = 0; n1 < N; ++n1) {
-          const float2 zv = g[brevc(n1, LP::lgL)];
-          col[xslot<N>(lam + N * j, n1) * RS] = n1 == 0 ? zv : cmul(zv, w.wv[j][n1]);
-        }
-      }
-      wave_lds_order();
-      float2 v[Q];
-#pragma unroll
-      for (int k1 = 0; k1 < Q; ++k1) v[k1] = col[xslot<N>(k1, lam) * RS];
-      dif_stages<Q, true, Q / 2>(v);
-#pragma unroll
-      for (int n2 = 0; n2 < Q / 2; ++n2) res[c][n2] = v[brevc(n2, LP::lgQ)];
-      wave_lds_order();
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-      for (int n2 = 0; n2 < Q / 2; ++n2) {
-        const int z = lam + N * n2;
-        if (z < nz) col[(c * ZR + z) * RS] = res[c][n2];
-      }
-  }
-  template <class KMul>
-  __device__ static void convolve(float2* col, int RS, int nz, int lam, const Tw& w, KMul&& kmul) {
-    Spec sp;
-    forward(col, RS, lam, w, sp);
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int p = 0; p < N; ++p) kmul(kz_of(lam, j, p), sp[0][j][p], sp[1][j][p], sp[2][j][p]);
-    inverse(col, RS, nz, lam, w, sp);
-  }
-};
-
-// LDS bank layout shared by the kernels below (64 banks of four bytes; an
-// eight-byte access is served 32 lanes per cycle).  Rows are an odd number of
-// slots apart.  A y row has N lanes, lane = lam * RPW + r in its wavefront
-// (RPW = 64 / N rows), and the wavefront's rows are SY = N / 2 apart, so the
-// 32 lanes of a half-wavefront (N / 2 values of lam, RPW rows) fall on
-// distinct bank pairs; the rows of SY wavefronts interleave to fill blocks of
-// 32 rows.  A z column has N consecutive lanes and the wavefront's columns
-// are SZ apart (SZ = N where the tile is wide enough), for the same reason.
-// Row of y-lane yrl in block g0 of wavefront `wave`:
-template <int N>
-__device__ __forceinline__ int yrow_of(int g0, int wave, int yrl) {
-  constexpr int SY = N / 2;
-  return 32 * g0 + wave % SY + SY * yrl;
-}
-// Column of thread t in a tile of NCOL columns, N lanes per column:
-template <int N, int NCOL>
-__device__ __forceinline__ int zcol_of(int t) {
-  constexpr int CPW = 64 / N, SZ = N < NCOL / CPW ? N : NCOL / CPW;
-  const int wz = t >> 6;
-  return wz % SZ + SZ * ((t & 63) / N) + SZ * CPW * (wz / SZ);
-}
-
 // Planes kx = 0 and kx = Px/2 of the x transform of real rows are real, and
 // in them the tensor components odd in x (xy, xz) vanish, so each plane's y-z
 // convolution is real as well.  Where one column per thread covers the padded
@@ -1445,104 +1119,6 @@ __global__ __launch_bounds__(MM_YZX_T) __attribute__((amdgpu_waves_per_eu(MY >= 
 // memory in the multiply (38 us), or replacing the first one in LDS between
 // the halves of the workgroup (35 us), was slower than putting it where the
 // rows were.
-
-// M-point transforms of one row of M slots by N lanes (lane lam), in place;
-// twm: W_M in LDS.
-template <int M>
-struct YFull {
-  static constexpr int Q = 16, N = M / Q, lgQ = 4, lgN = ilog2c(N);
-  static_assert(N >= 2 && N <= Q, "row length");
-  __device__ static void forward(float2* line, int lam, const float2* twm) {
-    float2 v[Q];
-#pragma unroll
-    for (int n1 = 0; n1 < Q; ++n1) v[n1] = line[N * n1 + lam];
-    dif_stages<Q, false, Q / 2>(v);
-    wave_lds_order();
-#pragma unroll
-    for (int p = 0; p < Q; ++p) {
-      const int k1 = brevc(p, lgQ);
-      line[xslot<N>(k1, lam)] = k1 ? cmul(v[p], twm[lam * k1]) : v[p];
-    }
-    wave_lds_order();
-    float2 u[Q / N][N];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j) {
-#pragma unroll
-      for (int a = 0; a < N; ++a) u[j][a] = line[xslot<N>(lam + N * j, a)];
-      dif_stages<N, false, N / 2>(u[j]);
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int p = 0; p < N; ++p) line[lam + N * j + Q * brevc(p, lgN)] = u[j][p];
-  }
-  // Row of A + iB (A, B real rows before the twist by W_2M^{rj}) to their
-  // spectra: A[k] = (X[k] + conj X[k']) / 2, B[k] = (X[k] - conj X[k']) / 2i
-  // with k' = M - k (r = 0) or M - 1 - k (r = 1), k < M/2, at slots
-  // SM::of(0, k) and SM::of(1, k); for r = 0 the real values at k = 0 and M/2
-  // share the slots of k = 0.
-  template <class SM>
-  __device__ static void split_pair(float2* line, int lam, int r) {
-    constexpr int H = M / 2, NI = H / N;
-    float2 x[NI], q[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lam + N * i;
-      x[i] = line[k];
-      q[i] = line[r ? M - 1 - k : k == 0 ? H : M - k];
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int k = lam + N * i;
-      const bool z = !r && k == 0;
-      line[SM::of(0, k)] = z ? make_float2(x[i].x, q[i].x) : make_float2(0.5f * (x[i].x + q[i].x), 0.5f * (x[i].y - q[i].y));
-      line[SM::of(1, k)] = z ? make_float2(x[i].y, q[i].y) : make_float2(0.5f * (x[i].y + q[i].y), 0.5f * (q[i].x - x[i].x));
-    }
-  }
-  // spectrum of A + iB at k from the two half spectra
-  template <class SM>
-  __device__ static float2 pair_value(const float2* line, int k, int r) {
-    constexpr int H = M / 2;
-    const bool lo = k < H;
-    const int m = lo ? k : r ? M - 1 - k : M - k;
-    const int i = m == H ? 0 : m;                 // (r = 0, k = M/2: the shared slot)
-    const float2 a = line[SM::of(0, i)], b = line[SM::of(1, i)];
-    if (!r && k == 0) return make_float2(a.x, b.x);
-    if (m == H) return make_float2(a.y, b.y);
-    return lo ? make_float2(a.x - b.y, a.y + b.x) : make_float2(a.x + b.y, b.x - a.y);
-  }
-  template <class SM = void>
-  __device__ static void inverse(float2* line, int lam, const float2* twm, int r) {
-    float2 g[Q / N][N];
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j) {
-#pragma unroll
-      for (int k2 = 0; k2 < N; ++k2) {
-        if constexpr (std::is_void_v<SM>) g[j][k2] = line[lam + N * j + Q * k2];
-        else g[j][k2] = pair_value<SM>(line, lam + N * j + Q * k2, r);
-      }
-      dif_stages<N, true, N / 2>(g[j]);
-    }
-    wave_lds_order();
-#pragma unroll
-    for (int j = 0; j < Q / N; ++j)
-#pragma unroll
-      for (int n1 = 0; n1 < N; ++n1) {
-        const float2 zv = g[j][brevc(n1, lgN)];
-        line[xslot<N>(lam + N * j, n1)] = n1 == 0 ? zv : cmul(zv, conjf2(twm[n1 * (lam + N * j)]));
-      }
-    wave_lds_order();
-    float2 v[Q];
-#pragma unroll
-    for (int k1 = 0; k1 < Q; ++k1) v[k1] = line[xslot<N>(k1, lam)];
-    dif_stages<Q, true, Q / 2>(v);
-    wave_lds_order();
-#pragma unroll
-    for (int n2 = 0; n2 < Q; ++n2) line[lam + N * n2] = v[brevc(n2, lgQ)];
-  }
-};
 
 // Layout of one workgroup: NZ lanes per z column, one column per lane group.
 // The half-spectrum columns of the two real planes (see YzxPairs) are placed
@@ -2034,8 +1610,12 @@ __global__ __launch_bounds__(MM_XR_T) void k_fft_xir(const InstDesc* __restrict_
 template <int DIR>
 __global__ __launch_bounds__(256) void k_fft_y(const InstDesc* __restrict__ descs,
                                                const WorkItem* __restrict__ work, int W,
-                                               const float2* __restrict__ tw) {
+                                               const float2* __restrict__ tw, int nwork, int fmethod, int fstage) {
   extern __shared__ float2 lds[];
+  if ((int)blockIdx.x >= nwork) {
+    final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
+    return;
+  }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
   if (gbl(D.ctl)->done) return;
@@ -2255,18 +1835,21 @@ hipError_t mmk_launch_fft_xi(int W, int nblocks, size_t lds, const InstDesc* d, 
 }
 
 hipError_t mmk_launch_fft_yz(int TK, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
-                             const float2* tw, hipStream_t s) {
-  MM_LAUNCH(mmk::k_fft_yz, dim3(nblocks), dim3(MM_YZ_T), lds, s, d, w, tw, TK);
+                             const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
+  if (nfinal < 0 || (nfinal > 0 && lds < MMI_PSTRIDE * sizeof(double))) return hipErrorInvalidValue;
+  MM_LAUNCH(mmk::k_fft_yz, dim3(nblocks + nfinal), dim3(MM_YZ_T), lds, s, d, w, tw, TK, nblocks, fmethod, fstage);
   return hipGetLastError();
 }
 
 #define MM_YZR_CASE(A, B)                                                                        \
   if (MY == A && MZ == B) {                                                                      \
-    MM_LAUNCH((mmk::k_fft_yzr<A, B>), dim3(nblocks), dim3(MM_YZR_T), lds, s, d, w, tw); \
+    MM_LAUNCH((mmk::k_fft_yzr<A, B>), dim3(nblocks + nfinal), dim3(MM_YZR_T), lds, s, d, w, tw, nblocks, fmethod, \
+              fstage);                                                                           \
     return hipGetLastError();                                                                    \
   }
 hipError_t mmk_launch_fft_yzr(int MY, int MZ, int nblocks, size_t lds, const InstDesc* d,
-                              const WorkItem* w, const float2* tw, hipStream_t s) {
+                              const WorkItem* w, const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
+  if (nfinal < 0 || (nfinal > 0 && lds < MMI_PSTRIDE * sizeof(double))) return hipErrorInvalidValue;
   MM_YZR_CASE(4, 4) MM_YZR_CASE(8, 4) MM_YZR_CASE(16, 4) MM_YZR_CASE(32, 4)
   MM_YZR_CASE(4, 8) MM_YZR_CASE(8, 8) MM_YZR_CASE(16, 8) MM_YZR_CASE(32, 8)
   MM_YZR_CASE(4, 16) MM_YZR_CASE(8, 16) MM_YZR_CASE(16, 16) MM_YZR_CASE(32, 16)
@@ -2372,9 +1955,10 @@ int mmk_sx_rows(int py) {
 }
 
 hipError_t mmk_launch_fft_y(int dir, int W, int nblocks, size_t lds, const InstDesc* d,
-                            const WorkItem* w, const float2* tw, hipStream_t s) {
-  if (dir < 0) MM_LAUNCH(mmk::k_fft_y<-1>, dim3(nblocks), dim3(256), lds, s, d, w, W, tw);
-  else MM_LAUNCH(mmk::k_fft_y<1>, dim3(nblocks), dim3(256), lds, s, d, w, W, tw);
+                            const WorkItem* w, const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
+  if (nfinal < 0 || (nfinal > 0 && (dir > 0 || lds < MMI_PSTRIDE * sizeof(double)))) return hipErrorInvalidValue;
+  if (dir < 0) MM_LAUNCH(mmk::k_fft_y<-1>, dim3(nblocks + nfinal), dim3(256), lds, s, d, w, W, tw, nblocks, fmethod, fstage);
+  else MM_LAUNCH(mmk::k_fft_y<1>, dim3(nblocks), dim3(256), lds, s, d, w, W, tw, nblocks, 0, 0);
   return hipGetLastError();
 }
 
@@ -2410,6 +1994,7 @@ hipError_t mmk_set_lds_limits() {
   if (e == hipSuccess)                                                                                     \
     e = hipFuncSetAttribute((const void*)mmk::k_fft_yzh<A, B>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   MM_YZH_EACH(MM_YZH_ATTR)
+  if (e == hipSuccess) e = mmk_set_short_lds_limits();
 #define MM_SX_ATTR(K)                                                                                      \
   if (e == hipSuccess) e = hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   MM_SX_ATTR((mmk::k_fft_ysx<16, -1>)) MM_SX_ATTR((mmk::k_fft_ysx<32, -1>)) MM_SX_ATTR((mmk::k_fft_ysx<64, -1>))

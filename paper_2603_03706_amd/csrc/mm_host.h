@@ -32,7 +32,8 @@ hipError_t mmk_launch_fft_xi(int W, int nblocks, size_t lds, const InstDesc* d, 
                              const float2* tw, hipStream_t s);
 // fused y-z with lines in registers: Py = 4 MY, Pz = 4 MZ, MY in {4,8,16,32}, MZ in {4,8,16}
 hipError_t mmk_launch_fft_yzr(int MY, int MZ, int nblocks, size_t lds, const InstDesc* d,
-                              const WorkItem* w, const float2* tw, hipStream_t s);
+                              const WorkItem* w, const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0,
+                              int fstage = 0);
 // the same with eight lanes per z column (512 threads): MY in {4,8,16,32}, MZ in {8,16}.
 // nfinal > 0 appends that many workgroups that run the finalisation of stage
 // fstage of method fmethod for instances 0 .. nfinal - 1.
@@ -46,6 +47,12 @@ int mmk_yzx_pad();
 // k_fft_yzx for padded (py, pz) carries the real planes kx = 0 and Px/2 of an
 // instance in one work item (item 0; no item Px/2), with 6 pz float2 more LDS
 bool mmk_yzx_pairs(int py, int pz);
+// y-z of few z planes: padded z of 4, 8 or 16 with padded y of 8..256, or one z plane with padded y of 8..512;
+// mmk_yzs_lds is 0 for other shapes
+size_t mmk_yzs_lds(int py, int pz);
+hipError_t mmk_launch_fft_yzs(int py, int pz, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
+                              const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0, int fstage = 0);
+hipError_t mmk_set_short_lds_limits();
 // y-z in two halves of the ky range (2 kx items per instance and the planes 0 and Px/2 in one pair of items):
 // padded y of 64..256, padded z of 32 or 64; mmk_yzh_lds is 0 for other shapes
 size_t mmk_yzh_lds(int py, int pz);
@@ -56,9 +63,10 @@ hipError_t mmk_launch_fft_ysx(int dir, int py, int nblocks, size_t lds, const In
                               int fstage = 0);
 int mmk_sx_rows(int py);
 hipError_t mmk_launch_fft_yz(int TK, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
-                             const float2* tw, hipStream_t s);
+                             const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0, int fstage = 0);
 hipError_t mmk_launch_fft_y(int dir, int W, int nblocks, size_t lds, const InstDesc* d,
-                            const WorkItem* w, const float2* tw, hipStream_t s);
+                            const WorkItem* w, const float2* tw, hipStream_t s, int nfinal = 0, int fmethod = 0,
+                            int fstage = 0);
 hipError_t mmk_launch_fft_zc(int TW, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
                              const float2* tw, hipStream_t s);
 hipError_t mmk_set_lds_limits();
