@@ -1207,61 +1207,32 @@ mm_status launch_piece(mm_batch* b) {
   return enqueue_small(b, b->gen_wg ? kStepsPerGraph : kSmallSteps);
 }
 
-// One reverse step of the discrete adjoint for every instance of the batch.
-mm_status enqueue_reverse_step_dp(mm_batch* b);
+// One reverse step of the discrete adjoint for every instance of the batch
+// (RK4: stages 4..1; the replayed steps of an adaptive run: stages 6..1 of the
+// Dormand-Prince tableau).  The cavity part rides on the step start and on
+// stage kernel B (see mmk_launch_adj).
 mm_status enqueue_reverse_step(mm_batch* b) {
-  if (b->method == MM_DP45) return enqueue_reverse_step_dp(b);
   const int n = (int)b->ctxs.size();
-  if (mm_status s = launch(b, "adj_start", [&] { return mmk_launch_adj(0, 0, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-    return s;
-  if (mm_status s = launch(b, "adj_cavity", [&] { return mmk_launch_adj(3, 5, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-    return s;
+  const bool dp = b->method == MM_DP45;
+  auto adj = [&](const char* name, int kind, int st) {
+    return launch(b, name, [&] {
+      return mmk_launch_adj(kind, dp, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream, g_twiddle, b->stage_lds);
+    });
+  };
+  if (mm_status s = adj("adj_start", 0, 0)) return s;
   // with the demag fields of the stage inputs recorded, only the convolution
   // of the field adjoint remains per stage
   const bool bd_recorded = b->ctxs.size() == 1 && b->ctxs[0]->desc.rec_bd;
-  for (int st = 4; st >= 1; --st) {
+  for (int st = dp ? 6 : 4; st >= 1; --st) {
     if (!bd_recorded)
       if (mm_status s = enqueue_demag(b, st, MMI_ADJ)) return s;
     // for groups with x passes in the cell kernels, the adjoint stage kernels
     // transform the field adjoint themselves (R2C in A, C2R in B)
-    if (mm_status s = launch(b, "adj_stage_a", [&] {
-          return mmk_launch_adj(1, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream, g_twiddle, b->stage_lds);
-        }))
-      return s;
+    if (mm_status s = adj("adj_stage_a", 1, st)) return s;
     if (mm_status s = enqueue_demag(b, 0, MMI_ADJ, false, false)) return s;
-    if (mm_status s = launch(b, "adj_stage_b", [&] {
-          return mmk_launch_adj(2, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream, g_twiddle, b->stage_lds);
-        }))
-      return s;
-    if (mm_status s = launch(b, "adj_cavity", [&] { return mmk_launch_adj(3, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-      return s;
-  }
-  return MM_OK;
-}
-
-// The same for the replayed steps of an adaptive run: stages 6..1 of the
-// Dormand-Prince tableau (cavity part: kind 4, stage 7 = step start).
-mm_status enqueue_reverse_step_dp(mm_batch* b) {
-  const int n = (int)b->ctxs.size();
-  if (mm_status s = launch(b, "adj_start", [&] { return mmk_launch_adj(0, 0, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-    return s;
-  if (mm_status s = launch(b, "adj_cavity", [&] { return mmk_launch_adj(4, 7, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-    return s;
-  const bool bd_recorded = b->ctxs.size() == 1 && b->ctxs[0]->desc.rec_bd;
-  for (int st = 6; st >= 1; --st) {
-    if (!bd_recorded)
-      if (mm_status s = enqueue_demag(b, st, MMI_ADJ)) return s;
-    if (mm_status s = launch(b, "adj_stage_a", [&] {
-          return mmk_launch_adj(1, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream, g_twiddle, b->stage_lds);
-        }))
-      return s;
-    if (mm_status s = enqueue_demag(b, 0, MMI_ADJ, false, false)) return s;
-    if (mm_status s = launch(b, "adj_stage_b", [&] {
-          return mmk_launch_adj(2, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream, g_twiddle, b->stage_lds);
-        }))
-      return s;
-    if (mm_status s = launch(b, "adj_cavity", [&] { return mmk_launch_adj(4, st, b->total_wg, n, b->d_desc, b->d_wg, b->stream); }))
-      return s;
+    if (mm_status s = adj("adj_stage_b", 2, st)) return s;
+    if (dp && st == 1)
+      if (mm_status s = adj("adj_cavity", 3, st)) return s;
   }
   return MM_OK;
 }

@@ -82,12 +82,164 @@ __device__ __forceinline__ double adj_step(const InstDesc& D, CtlPtr C) {
   return fabs(gbl(D.hlog)[C->adj_base + C->rec_index]);
 }
 
+// --------------------------------------------------------- cavity part
+// RK4 (DP = false): ST = 5 step start, ST = 4..1 after the stage kernels of
+// that stage.  DP45 (DP = true): ST = 7 step start, ST = 6..1.
+// It needs the partial sums of stage kernel A and nothing of stage kernel B,
+// which touches none of what it writes (but for the index of the recorded
+// step at the end of a DP45 step), so one workgroup per instance runs it
+// beside B's own in B's launch; the step start runs beside k_adj_start.  As
+// launches of their own, each slot summed by the whole workgroup in turn,
+// these took 27 us a stage on the 128x128x32 film (1024 records, four modes)
+// and 4 us and a launch on small grids: its reverse step 0.62 vs 0.74 ms, that
+// of the 8x8x1 geometry 38 vs 85 us.
+template <bool DP, int ST>
+__device__ void adj_cav(const InstDesc* __restrict__ descs, int inst, double* tot) {
+  constexpr bool kStart = DP ? ST == 7 : ST == 5;
+  const InstDesc& D = descs[inst];
+  InstCtl* C = D.ctl;
+  if (C->done) return;
+  const int N = D.N;
+  const double h = adj_step(D, C);
+  if (!kStart) {
+    // every slot is summed in a fixed order: a wavefront takes slots in turn,
+    // lane l records l, l + 64, ... (eight in flight), a butterfly joins them
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const MMG double* P = gbl(D.partials);
+    for (int k = wv; k < 3 * N + 4; k += MMI_WG / 64) {
+      const int q = k < N ? MMI_ASLOT_FB + k : k < 3 * N ? MMI_ASLOT_MM + (k - N) : MMI_ASLOT_ALPHA + (k - 3 * N);
+      double v = 0.0;
+      int w = lane;
+      for (; w + 7 * 64 < D.nwg; w += 8 * 64) {
+        double p[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = P[(size_t)(w + u * 64) * MMI_PSTRIDE + q];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += p[u];
+      }
+      for (; w < D.nwg; w += 64) v += P[(size_t)w * MMI_PSTRIDE + q];
+      v = wave_sum(v);
+      if (lane == 0) tot[q] = v;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
+  if (kStart) {
+    // a loss on the trace: its derivative at the end of the step being reversed
+    if (!DP && D.dla_trace) {
+      const double* q = D.dla_trace + (size_t)(C->adj_base + C->rec_index + 1) * N * 2;
+      for (int n = 0; n < N; ++n) {
+        C->la[n][0] += q[2 * n];
+        C->la[n][1] += q[2 * n + 1];
+      }
+    }
+    const double wl = DP ? h * DPCoef::b6 : h / 6.0;
+    for (int n = 0; n < N; ++n)
+      for (int r = 0; r < 2; ++r) {
+        C->lza[n][r] = C->la[n][r];
+        C->lka[n][r] = wl * C->la[n][r];
+      }
+  } else {
+    const double* as = D.rec_a + ((size_t)C->rec_index * D.rec_nstg + (ST - 1)) * N * 2;
+    const double scale = D.inv_ngeo / (double)D.S;
+    C->grad_alpha += tot[MMI_ASLOT_ALPHA];
+    for (int c = 0; c < 3; ++c) C->grad_B0[c] += tot[MMI_ASLOT_B0 + c];
+    const double cst = (ST == 4) ? h : 0.5 * h;
+    const double wprev = h * (ST == 2 ? 1.0 : 2.0) / 6.0;
+    // mu_a of every mode first: with direct mode coupling it reads the
+    // lambda_ka of all modes, which the update below overwrites
+    double mu[MMI_MAX_MODES][2];
+    for (int n = 0; n < N; ++n) {
+      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
+      const double lr = C->lka[n][0], li = C->lka[n][1];
+      const double fb = tot[MMI_ASLOT_FB + n];
+      const double mr = tot[MMI_ASLOT_MM + 2 * n] * scale, mi = tot[MMI_ASLOT_MM + 2 * n + 1] * scale;
+      // dF/dg = (s + i c) m^- ; feedback h0 = 2 g / gamma with Re[e^{-i Phi} a] = c ar + s ai
+      const double fr = s * mr - c * mi, fi = s * mi + c * mr;
+      C->grad_g[n] += lr * fr + li * fi + fb * (2.0 / D.gamma) * (c * as[2 * n] + s * as[2 * n + 1]);
+      // mu_a = conj(-kappa - i w) lambda_ka + h0 fb (c, s)
+      const double w = D.omega[n], kp = D.kappa[n];
+      double mur = -kp * lr - w * li + D.h0[n] * fb * c;
+      double mui = w * lr - kp * li + D.h0[n] * fb * s;
+      if (D.kerr_on) {
+        // transpose of the Jacobian of -i K |a|^2 a at the stage amplitude
+        const double ar = as[2 * n], ai = as[2 * n + 1], K = D.kerr[n];
+        const double q = K * (ar * ar + ai * ai), x = 2.0 * K * ar * ai;
+        mur += lr * x - li * (q + 2.0 * K * ar * ar);
+        mui += lr * (q + 2.0 * K * ai * ai) - li * x;
+      }
+      if (D.param_on) {
+        // transpose of the Jacobian of -i Lam conj(a), Lam = lam e^{-2 i wp t}
+        // at the stage time: [[Li, -Lr], [-Lr, -Li]] (symmetric)
+        const double ts = DP ? gbl(D.rec_t)[C->rec_index] + DPCoef::c(ST) * h
+                             : C->adj_t0 + (double)C->rec_index * h + (ST == 1 ? 0.0 : ST == 4 ? h : 0.5 * h);
+        double sn, cs;
+        sincos(2.0 * D.par_wp[n] * ts, &sn, &cs);
+        const double Lr = D.par_re[n] * cs + D.par_im[n] * sn;
+        const double Li = D.par_im[n] * cs - D.par_re[n] * sn;
+        mur += Li * lr - Lr * li;
+        mui -= Lr * lr + Li * li;
+      }
+      if (D.jcpl_on)
+        for (int q = 0; q < N; ++q) {
+          // -i sum_q J_qn a_n in the equation of mode q, J symmetric
+          mur -= D.jcpl[q][n] * C->lka[q][1];
+          mui += D.jcpl[q][n] * C->lka[q][0];
+        }
+      mu[n][0] = mur;
+      mu[n][1] = mui;
+    }
+    for (int n = 0; n < N; ++n) {
+      C->la[n][0] += mu[n][0];
+      C->la[n][1] += mu[n][1];
+      if (!DP) {
+        if (ST > 1) {
+          C->lka[n][0] = wprev * C->lza[n][0] + cst * mu[n][0];
+          C->lka[n][1] = wprev * C->lza[n][1] + cst * mu[n][1];
+        }
+      } else if (ST > 1) {
+        // lambda_ka(ST-1) = h (b_(ST-1) lambda_za + sum_{q>=ST} a_(q,ST-1) mu_a,q)
+        for (int r = 0; r < 2; ++r) {
+          if (ST >= 3) C->lmua[ST - 1][n][r] = mu[n][r];
+          double acc = DPCoef::b(ST - 1) * C->lza[n][r] + DPCoef::a(ST, ST - 1) * mu[n][r];
+          for (int q = ST + 1; q <= 6; ++q) acc += DPCoef::a(q, ST - 1) * C->lmua[q - 1][n][r];
+          C->lka[n][r] = h * acc;
+        }
+      }
+    }
+    if (ST == 1) C->rec_index -= 1;
+  }
+  // adjoint of m^- for the next stage kernel A: conj(i g e^{-i Phi}) lambda_ka
+  if (ST >= 2) {
+    for (int n = 0; n < N; ++n) {
+      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
+      const double lr = C->lka[n][0], li = C->lka[n][1];
+      // conj(g (s + i c)) = g (s - i c)
+      C->lmm[n][0] = g * (s * lr + c * li);
+      C->lmm[n][1] = g * (s * li - c * lr);
+    }
+  }
+}
+
+// the same as a launch of its own (the last stage of a DP45 step)
+template <bool DP, int ST>
+__global__ __launch_bounds__(MMI_WG) void k_adj_cav(const InstDesc* __restrict__ descs, int count) {
+  __shared__ double tot[MMI_PSTRIDE];
+  if ((int)blockIdx.x < count) adj_cav<DP, ST>(descs, blockIdx.x, tot);
+}
+
 // ---------------------------------------------------------- step start
 // lambda_z from the step-end adjoint (held in lam_y), lambda_y = lambda_z,
 // lambda_k4 = h/6 lambda_z.
+template <bool DP>
 __global__ __launch_bounds__(MMI_WG) void k_adj_start(const InstDesc* __restrict__ descs,
-                                                      const int* __restrict__ wg_inst) {
-  const int lblk = xcd_block();
+                                                      const int* __restrict__ wg_inst, int nblocks) {
+  __shared__ double tot[MMI_PSTRIDE];
+  if ((int)blockIdx.x >= nblocks) {
+    adj_cav<DP, DP ? 7 : 5>(descs, (int)blockIdx.x - nblocks, tot);
+    return;
+  }
+  const int lblk = xcd_block(nblocks);
   const InstDesc& D = descs[wg_inst[lblk]];
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) return;
@@ -126,7 +278,7 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_start(const InstDesc* __restrict
 
 // ------------------------------------------------------------ stage A
 template <int ST>
-__global__ __launch_bounds__(MMI_WG) void k_adj_a(const InstDesc* __restrict__ descs,
+__global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k_adj_a(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
                                                   const float2* __restrict__ tw) {
   __shared__ double sh[4 * (MMI_WG / 64)];
@@ -272,12 +424,17 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_a(const InstDesc* __restrict__ d
 }
 
 // ------------------------------------------------------------ stage B
-template <int ST>
-__global__ __launch_bounds__(MMI_WG) void k_adj_b(const InstDesc* __restrict__ descs,
+template <bool DP, int ST>
+__global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(8), amdgpu_num_sgpr(80))) void k_adj_b(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
-                                                  const float2* __restrict__ tw) {
+                                                  const float2* __restrict__ tw, int nblocks) {
+  __shared__ double tot[MMI_PSTRIDE];
   extern __shared__ float2 xl[];
-  const int lblk = xcd_block();
+  if ((int)blockIdx.x >= nblocks) {
+    adj_cav<DP, ST>(descs, (int)blockIdx.x - nblocks, tot);
+    return;
+  }
+  const int lblk = xcd_block(nblocks);
   const InstDesc& D = descs[wg_inst[lblk]];
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) return;
@@ -302,7 +459,7 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_b(const InstDesc* __restrict__ d
   MMG float* const lam_y = gbl(D.lam_y);
   MMG float* const lam_z = gbl(D.lam_z);
   MMG float* const lam_k = gbl(D.lam_k);
-  const bool dp = D.method == MMI_DP45;
+  constexpr bool dp = DP;
   const double h = adj_step(D, C);
   // RK4: coefficient of k_(ST-1) in y_ST and the weight of k_(ST-1)
   const float cst = (float)(ST == 4 ? h : 0.5 * h);
@@ -370,170 +527,38 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_b(const InstDesc* __restrict__ d
   }
 }
 
-// --------------------------------------------------------- cavity part
-// RK4 (DP = false): ST = 5 step start, ST = 4..1 after the stage kernels of
-// that stage.  DP45 (DP = true): ST = 7 step start, ST = 6..1.
-template <bool DP, int ST>
-__global__ __launch_bounds__(MMI_WG) void k_adj_cav(const InstDesc* __restrict__ descs, int count) {
-  __shared__ double sh[MMI_WG / 64];
-  __shared__ double tot[MMI_PSTRIDE];
-  constexpr bool kStart = DP ? ST == 7 : ST == 5;
-  if ((int)blockIdx.x >= count) return;
-  const InstDesc& D = descs[blockIdx.x];
-  InstCtl* C = D.ctl;
-  if (C->done) return;
-  const int N = D.N;
-  const double h = adj_step(D, C);
-  if (!kStart) {
-    for (int q = 0; q < MMI_PSTRIDE; ++q) {
-      const bool used = (q < N) || (q >= MMI_ASLOT_MM && q < MMI_ASLOT_MM + 2 * N) ||
-                        (q >= MMI_ASLOT_ALPHA && q < MMI_ASLOT_B0 + 3);
-      if (!used) continue;
-      double v = 0.0;
-      for (int w = threadIdx.x; w < D.nwg; w += MMI_WG) v += gbl(D.partials)[(size_t)w * MMI_PSTRIDE + q];
-      v = block_sum(v, sh);
-      if (threadIdx.x == 0) tot[q] = v;
-    }
-  }
-  if (threadIdx.x != 0) return;
-  if (kStart) {
-    // a loss on the trace: its derivative at the end of the step being reversed
-    if (!DP && D.dla_trace) {
-      const double* q = D.dla_trace + (size_t)(C->adj_base + C->rec_index + 1) * N * 2;
-      for (int n = 0; n < N; ++n) {
-        C->la[n][0] += q[2 * n];
-        C->la[n][1] += q[2 * n + 1];
-      }
-    }
-    const double wl = DP ? h * DPCoef::b6 : h / 6.0;
-    for (int n = 0; n < N; ++n)
-      for (int r = 0; r < 2; ++r) {
-        C->lza[n][r] = C->la[n][r];
-        C->lka[n][r] = wl * C->la[n][r];
-      }
-  } else {
-    const double* as = D.rec_a + ((size_t)C->rec_index * D.rec_nstg + (ST - 1)) * N * 2;
-    const double scale = D.inv_ngeo / (double)D.S;
-    C->grad_alpha += tot[MMI_ASLOT_ALPHA];
-    for (int c = 0; c < 3; ++c) C->grad_B0[c] += tot[MMI_ASLOT_B0 + c];
-    const double cst = (ST == 4) ? h : 0.5 * h;
-    const double wprev = h * (ST == 2 ? 1.0 : 2.0) / 6.0;
-    // mu_a of every mode first: with direct mode coupling it reads the
-    // lambda_ka of all modes, which the update below overwrites
-    double mu[MMI_MAX_MODES][2];
-    for (int n = 0; n < N; ++n) {
-      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
-      const double lr = C->lka[n][0], li = C->lka[n][1];
-      const double fb = tot[MMI_ASLOT_FB + n];
-      const double mr = tot[MMI_ASLOT_MM + 2 * n] * scale, mi = tot[MMI_ASLOT_MM + 2 * n + 1] * scale;
-      // dF/dg = (s + i c) m^- ; feedback h0 = 2 g / gamma with Re[e^{-i Phi} a] = c ar + s ai
-      const double fr = s * mr - c * mi, fi = s * mi + c * mr;
-      C->grad_g[n] += lr * fr + li * fi + fb * (2.0 / D.gamma) * (c * as[2 * n] + s * as[2 * n + 1]);
-      // mu_a = conj(-kappa - i w) lambda_ka + h0 fb (c, s)
-      const double w = D.omega[n], kp = D.kappa[n];
-      double mur = -kp * lr - w * li + D.h0[n] * fb * c;
-      double mui = w * lr - kp * li + D.h0[n] * fb * s;
-      if (D.kerr_on) {
-        // transpose of the Jacobian of -i K |a|^2 a at the stage amplitude
-        const double ar = as[2 * n], ai = as[2 * n + 1], K = D.kerr[n];
-        const double q = K * (ar * ar + ai * ai), x = 2.0 * K * ar * ai;
-        mur += lr * x - li * (q + 2.0 * K * ar * ar);
-        mui += lr * (q + 2.0 * K * ai * ai) - li * x;
-      }
-      if (D.param_on) {
-        // transpose of the Jacobian of -i Lam conj(a), Lam = lam e^{-2 i wp t}
-        // at the stage time: [[Li, -Lr], [-Lr, -Li]] (symmetric)
-        const double ts = DP ? gbl(D.rec_t)[C->rec_index] + DPCoef::c(ST) * h
-                             : C->adj_t0 + (double)C->rec_index * h + (ST == 1 ? 0.0 : ST == 4 ? h : 0.5 * h);
-        double sn, cs;
-        sincos(2.0 * D.par_wp[n] * ts, &sn, &cs);
-        const double Lr = D.par_re[n] * cs + D.par_im[n] * sn;
-        const double Li = D.par_im[n] * cs - D.par_re[n] * sn;
-        mur += Li * lr - Lr * li;
-        mui -= Lr * lr + Li * li;
-      }
-      if (D.jcpl_on)
-        for (int q = 0; q < N; ++q) {
-          // -i sum_q J_qn a_n in the equation of mode q, J symmetric
-          mur -= D.jcpl[q][n] * C->lka[q][1];
-          mui += D.jcpl[q][n] * C->lka[q][0];
-        }
-      mu[n][0] = mur;
-      mu[n][1] = mui;
-    }
-    for (int n = 0; n < N; ++n) {
-      C->la[n][0] += mu[n][0];
-      C->la[n][1] += mu[n][1];
-      if (!DP) {
-        if (ST > 1) {
-          C->lka[n][0] = wprev * C->lza[n][0] + cst * mu[n][0];
-          C->lka[n][1] = wprev * C->lza[n][1] + cst * mu[n][1];
-        }
-      } else if (ST > 1) {
-        // lambda_ka(ST-1) = h (b_(ST-1) lambda_za + sum_{q>=ST} a_(q,ST-1) mu_a,q)
-        for (int r = 0; r < 2; ++r) {
-          if (ST >= 3) C->lmua[ST - 1][n][r] = mu[n][r];
-          double acc = DPCoef::b(ST - 1) * C->lza[n][r] + DPCoef::a(ST, ST - 1) * mu[n][r];
-          for (int q = ST + 1; q <= 6; ++q) acc += DPCoef::a(q, ST - 1) * C->lmua[q - 1][n][r];
-          C->lka[n][r] = h * acc;
-        }
-      }
-    }
-    if (ST == 1) C->rec_index -= 1;
-  }
-  // adjoint of m^- for the next stage kernel A: conj(i g e^{-i Phi}) lambda_ka
-  if (ST >= 2) {
-    for (int n = 0; n < N; ++n) {
-      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
-      const double lr = C->lka[n][0], li = C->lka[n][1];
-      // conj(g (s + i c)) = g (s - i c)
-      C->lmm[n][0] = g * (s * lr + c * li);
-      C->lmm[n][1] = g * (s * li - c * lr);
-    }
-  }
-}
-
 }  // namespace mmk
 
-hipError_t mmk_launch_adj(int kind, int stage, int nblocks, int count, const InstDesc* d, const int* wg,
+// kind 0: step start, 1: stage kernel A, 2: stage kernel B; dp: the DP45 replay.
+// The cavity part of `count` instances rides on kinds 0 and 2, except on B of
+// stage 1 of a DP45 step, whose workgroups read what it changes: there it is a
+// launch of its own (kind 3).
+hipError_t mmk_launch_adj(int kind, bool dp, int stage, int nblocks, int count, const InstDesc* d, const int* wg,
                           hipStream_t s, const float2* tw, size_t lds) {
-  // kind 0: start, 1: A, 2: B, 3: cavity (RK4), 4: cavity (DP45)
   if (kind == 0) {
-    MM_LAUNCH(mmk::k_adj_start, dim3(nblocks), dim3(MMI_WG), 0, s, d, wg);
+    if (dp) MM_LAUNCH(mmk::k_adj_start<true>, dim3(nblocks + count), dim3(MMI_WG), 0, s, d, wg, nblocks);
+    else MM_LAUNCH(mmk::k_adj_start<false>, dim3(nblocks + count), dim3(MMI_WG), 0, s, d, wg, nblocks);
     return hipGetLastError();
   }
-#define MM_ADJ(K, ST)                                                                                  \
-  if (kind == K && stage == ST) {                                                                      \
-    if (K == 1) MM_LAUNCH(mmk::k_adj_a<ST>, dim3(nblocks), dim3(MMI_WG), lds, s, d, wg, tw);  \
-    if (K == 2) MM_LAUNCH(mmk::k_adj_b<ST>, dim3(nblocks), dim3(MMI_WG), lds, s, d, wg, tw);  \
-    return hipGetLastError();                                                                          \
-  }
-  MM_ADJ(1, 1) MM_ADJ(1, 2) MM_ADJ(1, 3) MM_ADJ(1, 4) MM_ADJ(1, 5) MM_ADJ(1, 6)
-  MM_ADJ(2, 1) MM_ADJ(2, 2) MM_ADJ(2, 3) MM_ADJ(2, 4) MM_ADJ(2, 5) MM_ADJ(2, 6)
-#undef MM_ADJ
-  if (kind == 3) {
-    switch (stage) {
-      case 1: MM_LAUNCH((mmk::k_adj_cav<false, 1>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 2: MM_LAUNCH((mmk::k_adj_cav<false, 2>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 3: MM_LAUNCH((mmk::k_adj_cav<false, 3>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 4: MM_LAUNCH((mmk::k_adj_cav<false, 4>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 5: MM_LAUNCH((mmk::k_adj_cav<false, 5>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      default: return hipErrorInvalidValue;
-    }
+  if (kind == 3 && dp && stage == 1) {
+    MM_LAUNCH((mmk::k_adj_cav<true, 1>), dim3(count), dim3(MMI_WG), 0, s, d, count);
     return hipGetLastError();
   }
-  if (kind == 4) {   // DP45 cavity part: stages 1..6, 7 = step start
-    switch (stage) {
-      case 1: MM_LAUNCH((mmk::k_adj_cav<true, 1>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 2: MM_LAUNCH((mmk::k_adj_cav<true, 2>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 3: MM_LAUNCH((mmk::k_adj_cav<true, 3>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 4: MM_LAUNCH((mmk::k_adj_cav<true, 4>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 5: MM_LAUNCH((mmk::k_adj_cav<true, 5>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 6: MM_LAUNCH((mmk::k_adj_cav<true, 6>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      case 7: MM_LAUNCH((mmk::k_adj_cav<true, 7>), dim3(count), dim3(MMI_WG), 0, s, d, count); break;
-      default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+#define MM_ADJ_A(ST)                                                                                  \
+  if (kind == 1 && stage == ST) {                                                                     \
+    MM_LAUNCH(mmk::k_adj_a<ST>, dim3(nblocks), dim3(MMI_WG), lds, s, d, wg, tw);                      \
+    return hipGetLastError();                                                                         \
   }
+#define MM_ADJ_B(DP, ST)                                                                              \
+  if (kind == 2 && dp == DP && stage == ST) {                                                         \
+    MM_LAUNCH((mmk::k_adj_b<DP, ST>), dim3(nblocks + (DP && ST == 1 ? 0 : count)), dim3(MMI_WG), lds, s, d, wg, tw, \
+              nblocks);                                                                               \
+    return hipGetLastError();                                                                         \
+  }
+  MM_ADJ_A(1) MM_ADJ_A(2) MM_ADJ_A(3) MM_ADJ_A(4) MM_ADJ_A(5) MM_ADJ_A(6)
+  MM_ADJ_B(false, 1) MM_ADJ_B(false, 2) MM_ADJ_B(false, 3) MM_ADJ_B(false, 4)
+  MM_ADJ_B(true, 1) MM_ADJ_B(true, 2) MM_ADJ_B(true, 3) MM_ADJ_B(true, 4) MM_ADJ_B(true, 5) MM_ADJ_B(true, 6)
+#undef MM_ADJ_A
+#undef MM_ADJ_B
   return hipErrorInvalidValue;
 }

@@ -237,11 +237,14 @@ __device__ __forceinline__ float2 conv_row(const InstDesc& D, const MMG float2* 
 // that each XCD works through one contiguous range of logical blocks: cells
 // that are neighbours in z, two 512-cell workgroups apart, are then read
 // through the same L2 instead of being fetched again by another XCD.
-__device__ __forceinline__ int xcd_block() {
-  const int nb = gridDim.x, b = blockIdx.x;
+// With nb given, it is the bijection on [0, nb) for launches that carry other
+// work in the blocks beyond.
+__device__ __forceinline__ int xcd_block(int nb) {
+  const int b = blockIdx.x;
   const int q = nb >> 3, r = nb & 7, x = b & 7;
   return x * q + min(x, r) + (b >> 3);
 }
+__device__ __forceinline__ int xcd_block() { return xcd_block((int)gridDim.x); }
 
 // Workgroup (of D.cpw cells) that the lw-th workgroup of an instance takes.
 // Where a z-plane is a whole number P >= 64 of full workgroups, consecutive
