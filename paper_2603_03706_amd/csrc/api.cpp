@@ -79,6 +79,7 @@ mm_status ensure_twiddles() {
   MM_HIP(hipMemcpy(g_twiddle, h.data(), sizeof(float2) * MMI_TW_LEN, hipMemcpyHostToDevice));
   MM_HIP(mmk_set_lds_limits());
   MM_HIP(mmk_set_small_lds_limits());
+  MM_HIP(mmk_set_small_adj_lds_limits());
   int dev = 0;
   MM_HIP(hipGetDevice(&dev));
   MM_HIP(hipDeviceGetAttribute(&g_cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1237,6 +1238,36 @@ mm_status enqueue_reverse_step(mm_batch* b) {
   return MM_OK;
 }
 
+// The reverse steps of one small instance run in one workgroup (k_small_adj) up
+// to two cells per thread.  us per reverse step with its recompute, one
+// workgroup vs the graph of nine launches: 64 cells 9.6 vs 47, 512 cells 13 vs
+// 56 (two sublattices 19 vs 75, these with sixteen profiled modes 71 vs 189),
+// 1024 cells 23 vs 59 (two sublattices 45 vs 82, these with sixteen modes 180
+// vs 227); with four cells per thread the adjoint vectors no longer fit in
+// registers: 62 vs 66, with sixteen modes 326 vs 264.
+// LDS: a stage input and lambda_B, then grad u and the profiles where they fit.
+bool small_reverse(const mm_batch* b) {
+  const mm_ctx* c = b->ctxs[0];
+  return b->ctxs.size() == 1 && small_fits(c->p, b->method, c->L.ncell) && small_per(c->L.ncell) <= 2;
+}
+
+mm_status enqueue_small_reverse(mm_batch* b, int64_t steps) {
+  const mm_ctx* c = b->ctxs[0];
+  const size_t nc = (size_t)c->L.ncell, n = (size_t)c->N * nc;
+  size_t lds = small_lds_m(c->p.sublattices, c->L.ncell);
+  const bool g_lds = lds + sizeof(double) * n <= MMI_SMALL_LDS;
+  if (g_lds) lds += sizeof(double) * n;
+  const bool u_lds = c->profiled && lds + sizeof(float) * n <= MMI_SMALL_LDS;
+  if (u_lds) lds += sizeof(float) * n;
+  for (int64_t left = steps; left > 0; left -= kSmallSteps)
+    if (mm_status s = launch(b, "small_adj", [&] {
+          return mmk_launch_small_adj(c->p.sublattices, c->L.ncell, lds, g_lds, u_lds, b->d_desc, 0,
+                                      (int)std::min<int64_t>(left, kSmallSteps), b->stream);
+        }))
+      return s;
+  return MM_OK;
+}
+
 mm_status ensure_reverse_graph(mm_batch* b) {
   if (b->exec_rev) return MM_OK;
   MM_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
@@ -2352,7 +2383,9 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
   }
   mm_batch* b = c->solo;
   if (mm_status s = refresh_descs(b)) return s;
-  if (mm_status s = ensure_reverse_graph(b)) return s;
+  const bool small = small_reverse(b);
+  if (!small)
+    if (mm_status s = ensure_reverse_graph(b)) return s;
   const auto t0 = std::chrono::steady_clock::now();
   for (int k = c->rec_nck - 1; k >= 0; --k) {
     const long long steps = std::min<long long>(K, c->rec_steps - (long long)k * K);
@@ -2381,7 +2414,11 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
     h.adj_h = c->rec_h;
     h.adj_t0 = c->ck_ctl[k].t;
     if (mm_status s = ctl_push(c, h)) return s;
-    for (long long q = 0; q < steps; ++q) MM_HIP(hipGraphLaunch(b->exec_rev, b->stream));
+    if (small) {
+      if (mm_status s = enqueue_small_reverse(b, steps)) return s;
+    } else {
+      for (long long q = 0; q < steps; ++q) MM_HIP(hipGraphLaunch(b->exec_rev, b->stream));
+    }
     MM_HIP(hipStreamSynchronize(b->stream));
   }
   const double wall = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();

@@ -34,25 +34,12 @@
 #include "kernels_common.h"
 #include "launch.h"
 #include "stage_final.h"
+#include "small_desc.h"
 
 namespace mmk {
 
 constexpr int SM_CELLS_T = 512;               // cell threads at most: cells t, t + 512, ... of thread t
 constexpr int SM_T = SM_CELLS_T + 64;         // and the cavity wavefront
-
-// The members of InstDesc that the field and the torque of a cell use.
-template <int NS>
-struct CellDesc {
-  static constexpr int S = NS;
-  int ncell, demag;
-  float cex_x, cex_y, cex_z, cK, ex, ey, ez, B0x, B0y, B0z, nlx, nly, nlz, BE, gl, alpha;
-  float csign[2];
-  float* bd;
-  __device__ __forceinline__ explicit CellDesc(const InstDesc& D)
-      : ncell(D.ncell), demag(D.demag), cex_x(D.cex_x), cex_y(D.cex_y), cex_z(D.cex_z), cK(D.cK), ex(D.ex),
-        ey(D.ey), ez(D.ez), B0x(D.B0x), B0y(D.B0y), B0z(D.B0z), nlx(D.nlx), nly(D.nly), nlz(D.nlz), BE(D.BE), gl(D.gl),
-        alpha(D.alpha), csign{D.csign[0], D.csign[1]}, bd(nullptr) {}
-};
 
 // One mode's parameters behind the names cav_rhs uses.
 struct ModeDesc {
@@ -87,13 +74,6 @@ __device__ __forceinline__ void cav_sincos(const ModeDesc&, double x, double& sn
   const double2 r = sincos_call(x);
   cs = r.x;
   sn = r.y;
-}
-
-// orders LDS accesses of the lanes of one wavefront (they complete in issue order)
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 struct Cplx {

@@ -22,6 +22,11 @@ hipError_t mmk_launch_stage(int method, int stage, bool final_pass, int nblocks,
 hipError_t mmk_launch_small_rk4(int S, int ncell, bool profiled, int nblocks, size_t lds, const InstDesc* d, const int* list, int steps,
                                 hipStream_t s);
 hipError_t mmk_set_small_lds_limits();
+// `steps` reverse steps of instance `inst` of S sublattices and ncell <= 1024 cells;
+// lds: dynamic LDS, with grad u (g_lds) and the profiles (u_lds) in it where they are kept there
+hipError_t mmk_launch_small_adj(int S, int ncell, size_t lds, bool g_lds, bool u_lds, const InstDesc* d, int inst, int steps,
+                                hipStream_t s);
+hipError_t mmk_set_small_adj_lds_limits();
 // x passes with lines in registers: Px = 4 MX, MX in {4, 8, 16, 32}; dir +1 forward (method,
 // stage select the stage input), -1 inverse; work items are tiles of 128 rows
 hipError_t mmk_launch_fft_xr(int dir, int MX, int nblocks, const InstDesc* d, const WorkItem* w, int method,
