@@ -318,7 +318,75 @@ mm_status validate(const mm_params* p) {
 }  // namespace
 
 // ================================================================== context
+// Pinned host buffers of kStageBytes for the exchanges of kernels_io.hip: one
+// per call under way, taken from a list that keeps at most kStageKeep of them
+// and is emptied when the last context is destroyed.
+constexpr size_t kStageBytes = 256 * 1024;
+constexpr size_t kStageKeep = 4;
+struct StagePool {
+  std::mutex mu;
+  std::vector<char*> free;
+  int64_t users = 0;
+};
+StagePool& stage_pool() {
+  static StagePool* p = new StagePool;   // (never destroyed: contexts may outlive static objects)
+  return *p;
+}
+struct StageUser {
+  StageUser() {
+    std::lock_guard<std::mutex> lk(stage_pool().mu);
+    ++stage_pool().users;
+  }
+  ~StageUser() {
+    std::vector<char*> drop;
+    {
+      std::lock_guard<std::mutex> lk(stage_pool().mu);
+      if (--stage_pool().users == 0) drop.swap(stage_pool().free);
+    }
+    for (char* p : drop) hipHostFree(p);
+  }
+  StageUser(const StageUser&) = delete;
+  StageUser& operator=(const StageUser&) = delete;
+};
+// A buffer for the length of one call, with the context's device current
+// meanwhile; p is null where `bytes` does not fit or none can be had.
+struct Stage {
+  char* p = nullptr;
+  int prev = -1;
+  Stage(int dev, size_t bytes) {
+    if (bytes > kStageBytes) return;
+    int cur = 0;
+    if (hipGetDevice(&cur) != hipSuccess || (cur != dev && hipSetDevice(dev) != hipSuccess)) return;
+    if (cur != dev) prev = cur;
+    {
+      std::lock_guard<std::mutex> lk(stage_pool().mu);
+      if (!stage_pool().free.empty()) {
+        p = stage_pool().free.back();
+        stage_pool().free.pop_back();
+      }
+    }
+    void* q = nullptr;
+    if (!p && hipHostMalloc(&q, kStageBytes, hipHostMallocPortable) == hipSuccess) p = (char*)q;
+    if (!p) (void)hipGetLastError();
+  }
+  ~Stage() {
+    if (p) {
+      std::unique_lock<std::mutex> lk(stage_pool().mu);
+      if (stage_pool().free.size() < kStageKeep) {
+        stage_pool().free.push_back(p);
+      } else {
+        lk.unlock();
+        hipHostFree(p);
+      }
+    }
+    if (prev >= 0) hipSetDevice(prev);
+  }
+  Stage(const Stage&) = delete;
+  Stage& operator=(const Stage&) = delete;
+};
+
 struct mm_ctx {
+  StageUser stage_user;
   mm_params p{};
   std::vector<uint8_t> geom;
   long long n_geo = 0;
@@ -369,9 +437,11 @@ struct mm_ctx {
   int64_t rec_steps = 0;
   int rec_K = 0, rec_nck = 0;
   double rec_h = 0.0;
-  float* ck_m = nullptr;           // checkpoints [nck][S*3*cells]
+  float* ck_m = nullptr;           // checkpoints [nck][S*3*cells], of ck_cap floats
+  size_t ck_cap = 0;
   std::vector<InstCtl> ck_ctl;
-  float* adj_f = nullptr;          // rec_m, rec_norm, lam_y, lam_k, lam_z, mu, lam_B
+  float* adj_f = nullptr;          // rec_m, rec_norm, lam_y, lam_k, lam_z, mu, lam_B, ...
+  float* adj_end = nullptr;        // in adj_f: the state after the recorded run, during mm_adjoint
   double* adj_d = nullptr;         // rec_a, grad_u
   int adj_K = -1, adj_N = -1, adj_nstg = 4;
   bool adj_on = false;             // descriptor carries the adjoint pointers
@@ -490,6 +560,23 @@ mm_status ctl_pull(const mm_ctx* c, InstCtl& h) {
 
 mm_status ctl_push(mm_ctx* c, const InstCtl& h) {
   MM_HIP(hipMemcpy(c->ws + c->L.ctl, &h, sizeof(InstCtl), hipMemcpyHostToDevice));
+  return MM_OK;
+}
+
+// The control block and (m not null) the mb bytes of the current state.
+mm_status state_pull(const mm_ctx* c, InstCtl& h, float* m, size_t mb) {
+  Stage stage(c->dev, sizeof(InstCtl) + mb);
+  const char* w = c->ws;
+  if (!stage.p) {
+    if (mm_status s = ctl_pull(c, h)) return s;
+    if (m) MM_HIP(hipMemcpy(m, w + c->L.y[h.cur], mb, hipMemcpyDeviceToHost));
+    return MM_OK;
+  }
+  MM_HIP(mmk_launch_state_out((const InstCtl*)(w + c->L.ctl), (const float*)(w + c->L.y[0]), (const float*)(w + c->L.y[1]),
+                              (int)(mb / sizeof(float)), stage.p));
+  MM_HIP(hipStreamSynchronize(nullptr));
+  std::memcpy(&h, stage.p, sizeof(InstCtl));
+  if (m) std::memcpy(m, stage.p + sizeof(InstCtl), mb);
   return MM_OK;
 }
 
@@ -1302,37 +1389,34 @@ mm_status check_ready(mm_ctx* c) {
 // Set run parameters of every instance; t_end = t + T (T <= 0: unbounded),
 // or t_end_abs when that is finite.
 mm_status begin_run(mm_batch* b, double T, double tol, double t_end_abs = NAN) {
-  for (mm_ctx* c : b->ctxs) {
-    InstCtl h;
-    if (mm_status s = ctl_pull(c, h)) return s;
-    h.t_end = std::isfinite(t_end_abs) ? t_end_abs : T > 0 ? h.t + T : 1e300;
-    h.tol = tol;
-    h.dt_fixed = c->dt0;
-    h.dt_min = c->dt_min;
-    h.dt_max = c->dt_max;
-    h.done = 0;
-    h.status = 0;
-    // the run-start stage kernel evaluates the feedback from the stage
-    // amplitude: it must be the amplitude of the state the run starts from
-    // (a previous run leaves the next stage input there, mm_set_a and
-    // mm_set_state set a alone)
-    for (int n = 0; n < MMI_MAX_MODES; ++n) {
-      h.as[n][0] = h.a[n][0];
-      h.as[n][1] = h.a[n][1];
-    }
-    h.rec_index = c->record_next;
+  auto args = [&](mm_ctx* c) {
+    MmRunArgs r{(InstCtl*)(c->ws + c->L.ctl), T, t_end_abs, tol, c->dt0, c->dt_min, c->dt_max, c->record_next, 0, 0, 0, 0.0, 0, 0};
     c->record_next = -1;
     if (c->sampling_changed) {
       c->sampling_changed = false;
-      h.trace_on = c->max_samples > 0 ? 1 : 0;
-      h.trace_started = 0;
-      h.trace_n = 0;
-      h.trace_steps = 0;
-      h.trace_max = c->max_samples;
-      h.trace_dt = c->dt_sample;
-      h.trace_stride = c->method == MM_RK4 ? std::max<long long>(1, llround(c->dt_sample / c->dt0)) : 1;
+      r.sampling = 1;
+      r.trace_on = c->max_samples > 0 ? 1 : 0;
+      r.trace_max = c->max_samples;
+      r.trace_dt = c->dt_sample;
+      r.trace_stride = c->method == MM_RK4 ? std::max<long long>(1, llround(c->dt_sample / c->dt0)) : 1;
     }
-    if (mm_status s = ctl_push(c, h)) return s;
+    return r;
+  };
+  // every instance's control block in one exchange; one instance (which a run
+  // that must not allocate is) by copies
+  const size_t n = b->ctxs.size();
+  Stage stage(b->ctxs[0]->dev, n > 1 ? sizeof(MmRunArgs) * n : kStageBytes + 1);
+  if (stage.p) {
+    for (size_t i = 0; i < n; ++i) ((MmRunArgs*)stage.p)[i] = args(b->ctxs[i]);
+    MM_HIP(mmk_launch_run_begin((const MmRunArgs*)stage.p, (int)n));
+    MM_HIP(hipStreamSynchronize(nullptr));
+  } else {
+    for (mm_ctx* c : b->ctxs) {
+      InstCtl h;
+      if (mm_status s = ctl_pull(c, h)) return s;
+      mm_apply_run(h, args(c));
+      if (mm_status s = ctl_push(c, h)) return s;
+    }
   }
   if (mm_status s = refresh_descs(b)) return s;
   if (mm_status s = wait_user_streams(b)) return s;
@@ -1340,7 +1424,8 @@ mm_status begin_run(mm_batch* b, double T, double tol, double t_end_abs = NAN) {
 }
 
 // The host copy of an instance's statistics from its control block.
-void set_stats(mm_ctx* c, const InstCtl& h, double wall) {
+template <class H>
+void set_stats(mm_ctx* c, const H& h, double wall) {
   c->stats.accepted = h.accepted;
   c->stats.rejected = h.rejected;
   c->stats.t = h.t;
@@ -1354,11 +1439,25 @@ void set_stats(mm_ctx* c, const InstCtl& h, double wall) {
 mm_status end_run(mm_batch* b, double wall) {
   MM_HIP(hipStreamSynchronize(b->stream));
   mm_status first = MM_OK;
-  for (mm_ctx* c : b->ctxs) {
-    InstCtl h;
-    if (mm_status s = ctl_pull(c, h)) return s;
+  auto take = [&](mm_ctx* c, const auto& h) {
     set_stats(c, h, wall);
     if (h.status != 0 && first == MM_OK) first = (mm_status)h.status;
+  };
+  const size_t n = b->ctxs.size();
+  Stage stage(b->ctxs[0]->dev, n > 1 ? (sizeof(InstCtl*) + sizeof(MmRunStats)) * n : kStageBytes + 1);
+  if (stage.p) {
+    auto* out = (MmRunStats*)stage.p;
+    auto** ctl = (InstCtl**)(out + n);
+    for (size_t i = 0; i < n; ++i) ctl[i] = (InstCtl*)(b->ctxs[i]->ws + b->ctxs[i]->L.ctl);
+    MM_HIP(mmk_launch_run_stats(ctl, out, (int)n));
+    MM_HIP(hipStreamSynchronize(nullptr));
+    for (size_t i = 0; i < n; ++i) take(b->ctxs[i], out[i]);
+  } else {
+    for (mm_ctx* c : b->ctxs) {
+      InstCtl h;
+      if (mm_status s = ctl_pull(c, h)) return s;
+      take(c, h);
+    }
   }
   if (first == MM_ERR_DT_UNDERFLOW) return fail(first, "adaptive step fell below dt_min");
   if (first == MM_ERR_NONFINITE) return fail(first, "state became non-finite");
@@ -1990,10 +2089,7 @@ mm_status mm_get_m(const mm_ctx* c, float* out) {
   if (!c || !out) return fail(MM_ERR_ARG, "NULL argument");
   if (!c->dev_ready || !c->m_set) return fail(MM_ERR_STATE, "no state on the device");
   InstCtl h;
-  if (mm_status s = ctl_pull(c, h)) return s;
-  MM_HIP(hipMemcpy(out, c->ws + c->L.y[h.cur], sizeof(float) * 3 * c->p.sublattices * (size_t)c->L.ncell,
-                   hipMemcpyDeviceToHost));
-  return MM_OK;
+  return state_pull(c, h, out, sizeof(float) * 3 * c->p.sublattices * (size_t)c->L.ncell);
 }
 
 mm_status mm_get_a(const mm_ctx* c, double* out) {
@@ -2001,7 +2097,7 @@ mm_status mm_get_a(const mm_ctx* c, double* out) {
   if (!c || !out) return fail(MM_ERR_ARG, "NULL argument");
   if (!c->dev_ready) return fail(MM_ERR_STATE, "no state on the device");
   InstCtl h;
-  if (mm_status s = ctl_pull(c, h)) return s;
+  if (mm_status s = state_pull(c, h, nullptr, 0)) return s;
   for (int n = 0; n < c->N; ++n) {
     out[2 * n] = h.a[n][0];
     out[2 * n + 1] = h.a[n][1];
@@ -2013,6 +2109,25 @@ mm_status mm_get_trace(const mm_ctx* c, double* t, double* a, double* mminus, in
   if (c && c->open_in) return open_error();
   if (!c || !n) return fail(MM_ERR_ARG, "NULL argument");
   if (!c->dev_ready) return fail(MM_ERR_STATE, "no state on the device");
+  const int64_t most = c->trace ? std::max<int64_t>(0, std::min<int64_t>(*n, c->trace_cap)) : 0;
+  if (most > 0 && most <= (int64_t)(kStageBytes / sizeof(double))) {
+    Stage stage(c->dev, sizeof(double) * (1 + (size_t)most * (1 + 4 * c->N)));
+    if (stage.p) {
+      const double* o = (const double*)stage.p;
+      MM_HIP(mmk_launch_trace_out((const InstCtl*)(c->ws + c->L.ctl), c->trace, c->trace_cap, c->N, most, (double*)stage.p));
+      MM_HIP(hipStreamSynchronize(nullptr));
+      const int64_t cnt = (int64_t)o[0];
+      if (cnt > 0) {
+        if (!t || !a || !mminus) return fail(MM_ERR_ARG, "NULL output buffer");
+        const size_t w = sizeof(double) * cnt;
+        std::memcpy(t, o + 1, w);
+        std::memcpy(a, o + 1 + most, w * 2 * c->N);
+        std::memcpy(mminus, o + 1 + most * (1 + 2 * c->N), w * 2 * c->N);
+      }
+      *n = cnt;
+      return MM_OK;
+    }
+  }
   InstCtl h;
   if (mm_status s = ctl_pull(c, h)) return s;
   const int64_t have = c->trace ? h.trace_n : 0;
@@ -2061,9 +2176,8 @@ mm_status mm_get_state(const mm_ctx* c, void* blob, size_t* bytes) {
   char* o = (char*)blob;
   std::memcpy(o, &hd, sizeof(hd));
   InstCtl h;
-  if (mm_status s = ctl_pull(c, h)) return s;
+  if (mm_status s = state_pull(c, h, (float*)(o + sizeof(hd) + sizeof(h)), mb)) return s;
   std::memcpy(o + sizeof(hd), &h, sizeof(h));
-  MM_HIP(hipMemcpy(o + sizeof(hd) + sizeof(h), c->ws + c->L.y[h.cur], mb, hipMemcpyDeviceToHost));
   *bytes = need;
   return MM_OK;
 }
@@ -2081,15 +2195,24 @@ mm_status mm_set_state(mm_ctx* c, const void* blob, size_t bytes) {
   if (mm_status s = ensure_device(c)) return s;
   InstCtl h;
   std::memcpy(&h, (const char*)blob + sizeof(hd), sizeof(h));
+  h.cur = 0;
+  h.rec_index = -1;
+  for (int j = 0; j < 8; ++j) h.slot[j] = j;
+  Stage stage(c->dev, sizeof(InstCtl) + mb);
+  if (stage.p) {   // (the kernel leaves this context's trace settings alone)
+    std::memcpy(stage.p, &h, sizeof(h));
+    std::memcpy(stage.p + sizeof(h), (const char*)blob + sizeof(hd) + sizeof(h), mb);
+    MM_HIP(mmk_launch_state_in((InstCtl*)(c->ws + c->L.ctl), (float*)(c->ws + c->L.y[0]), (int)(mb / sizeof(float)), stage.p));
+    MM_HIP(hipStreamSynchronize(nullptr));
+    c->m_set = true;
+    return MM_OK;
+  }
   InstCtl cur;
   if (mm_status s = ctl_pull(c, cur)) return s;
   // keep this context's trace settings
   h.trace_n = cur.trace_n; h.trace_max = cur.trace_max; h.trace_steps = cur.trace_steps;
   h.trace_stride = cur.trace_stride; h.trace_t0 = cur.trace_t0; h.trace_dt = cur.trace_dt;
   h.trace_on = cur.trace_on; h.trace_started = cur.trace_started;
-  h.cur = 0;
-  h.rec_index = -1;
-  for (int j = 0; j < 8; ++j) h.slot[j] = j;
   if (mm_status s = ctl_push(c, h)) return s;
   MM_HIP(hipMemcpy(c->ws + c->L.y[0], (const char*)blob + sizeof(hd) + sizeof(h), mb, hipMemcpyHostToDevice));
   c->m_set = true;
@@ -2118,6 +2241,15 @@ void restore_forward(InstCtl& dst, const InstCtl& ck) {
 }
 }  // namespace
 
+static mm_status ensure_checkpoints(mm_ctx* c, size_t floats) {
+  if (c->ck_m && c->ck_cap >= floats) return MM_OK;
+  if (c->ck_m) hipFree(c->ck_m);
+  c->ck_m = nullptr;
+  if (hipMalloc(&c->ck_m, sizeof(float) * floats) != hipSuccess) return fail(MM_ERR_OOM, "checkpoint allocation failed");
+  c->ck_cap = floats;
+  return MM_OK;
+}
+
 mm_status mm_run_record(mm_ctx* c, double T, int32_t every) {
   if (c && c->open_in) return open_error();
   if (!c) return fail(MM_ERR_ARG, "NULL context");
@@ -2134,9 +2266,7 @@ mm_status mm_run_record(mm_ctx* c, double T, int32_t every) {
   if (mm_status s = ensure_solo(c)) return s;
   const int nck = (int)((nsteps + every - 1) / every);
   const size_t vec = (size_t)3 * c->p.sublattices * c->L.ncell;
-  if (c->ck_m) hipFree(c->ck_m);
-  c->ck_m = nullptr;
-  if (hipMalloc(&c->ck_m, sizeof(float) * vec * nck) != hipSuccess) return fail(MM_ERR_OOM, "checkpoint allocation failed");
+  if (mm_status s = ensure_checkpoints(c, vec * nck)) return s;
   c->ck_ctl.assign(nck, InstCtl{});
   c->rec_have = false;
   long long left = nsteps;
@@ -2240,9 +2370,7 @@ mm_status mm_run_record_adaptive(mm_ctx* c, double T, double tol, int32_t every)
   c->rec_t_end = hend.t_end;
   // 2. checkpoints every `every` steps along the replay of the logged steps
   const int nck = (int)((n + every - 1) / every);
-  if (c->ck_m) hipFree(c->ck_m);
-  c->ck_m = nullptr;
-  if (hipMalloc(&c->ck_m, sizeof(float) * vec * nck) != hipSuccess) return fail(MM_ERR_OOM, "checkpoint allocation failed");
+  if (mm_status s = ensure_checkpoints(c, vec * nck)) return s;
   c->ck_ctl.assign(nck, InstCtl{});
   {
     InstCtl h = h0;
@@ -2343,15 +2471,16 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
     c->adj_f = nullptr;
     c->adj_d = nullptr;
     c->adj_K = -1;
-    // stage inputs, norms, five adjoint vectors and, with FFT demag, the demag
+    // stage inputs, norms, five adjoint vectors, the end state and, with FFT demag, the demag
     // field of every recorded stage input (the reverse pass then needs one
     // convolution per stage instead of two); DP45: the mu of stages 3..6 and
     // the start time of every step
-    const size_t nf = (size_t)(K + 1) * ns * vec + (size_t)K * S * nc + 5 * vec +
+    const size_t nf = (size_t)(K + 1) * ns * vec + (size_t)K * S * nc + 6 * vec +
                       (c->L.fft ? (size_t)(K + (dp ? 1 : 0)) * ns * 3 * nc : 0) + (dp ? 4 * vec : 0);
     const size_t nd = (size_t)K * ns * std::max(1, N) * 2 + (size_t)std::max(1, N) * nc + (dp ? (size_t)K : 0);
     if (hipMalloc(&c->adj_f, sizeof(float) * nf) != hipSuccess) return fail(MM_ERR_OOM, "adjoint allocation failed");
     if (hipMalloc(&c->adj_d, sizeof(double) * nd) != hipSuccess) return fail(MM_ERR_OOM, "adjoint allocation failed");
+    c->adj_end = c->adj_f + nf - vec;
     c->adj_K = K;
     c->adj_N = N;
     c->adj_nstg = ns;
@@ -2361,8 +2490,7 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
   // the end state, restored afterwards
   InstCtl end;
   if (mm_status s = ctl_pull(c, end)) return s;
-  std::vector<float> m_end(vec);
-  MM_HIP(hipMemcpy(m_end.data(), c->ws + c->L.y[end.cur], sizeof(float) * vec, hipMemcpyDeviceToHost));
+  MM_HIP(hipMemcpy(c->adj_end, c->ws + c->L.y[end.cur], sizeof(float) * vec, hipMemcpyDeviceToDevice));
   // initial adjoint
   {
     InstCtl h = end;
@@ -2376,9 +2504,8 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
     h.grad_B0[0] = h.grad_B0[1] = h.grad_B0[2] = 0.0;
     h.adj_h = c->rec_h;
     if (mm_status s = ctl_push(c, h)) return s;
-    std::vector<float> l0(vec, 0.f);
-    if (dL_dm) std::memcpy(l0.data(), dL_dm, sizeof(float) * vec);
-    MM_HIP(hipMemcpy(c->desc.lam_y, l0.data(), sizeof(float) * vec, hipMemcpyHostToDevice));
+    if (dL_dm) MM_HIP(hipMemcpy(c->desc.lam_y, dL_dm, sizeof(float) * vec, hipMemcpyHostToDevice));
+    else MM_HIP(hipMemset(c->desc.lam_y, 0, sizeof(float) * vec));
     MM_HIP(hipMemset(c->desc.grad_u, 0, sizeof(double) * std::max(1, N) * nc));
   }
   mm_batch* b = c->solo;
@@ -2436,9 +2563,11 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
     }
   if (grad_m0) MM_HIP(hipMemcpy(grad_m0, c->desc.lam_y, sizeof(float) * vec, hipMemcpyDeviceToHost));
   if (grad_u && N > 0) {
-    std::vector<double> gu((size_t)N * nc);
-    MM_HIP(hipMemcpy(gu.data(), c->desc.grad_u, sizeof(double) * gu.size(), hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < gu.size(); ++i) grad_u[i] = (float)gu[i];
+    // rounded on the device, in the stage records (at least 24 floats a cell,
+    // N <= 16), which are spent
+    float* f = c->desc.rec_m;
+    MM_HIP(mmk_launch_to_float(c->desc.grad_u, f, (size_t)N * nc));
+    MM_HIP(hipMemcpy(grad_u, f, sizeof(float) * (size_t)N * nc, hipMemcpyDeviceToHost));
   }
   // back to the end state of the recorded run
   InstCtl fin = h;
@@ -2449,7 +2578,8 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
   fin.done = end.done;
   fin.trace_on = end.trace_on;
   if (mm_status s = ctl_push(c, fin)) return s;
-  MM_HIP(hipMemcpy(c->ws + c->L.y[end.cur], m_end.data(), sizeof(float) * vec, hipMemcpyHostToDevice));
+  MM_HIP(hipMemcpy(c->ws + c->L.y[end.cur], c->adj_end, sizeof(float) * vec, hipMemcpyDeviceToDevice));
+  MM_HIP(hipStreamSynchronize(nullptr));
   c->stats.wall_s = wall;
   return MM_OK;
 }

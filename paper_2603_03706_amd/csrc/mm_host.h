@@ -12,6 +12,55 @@ int padded(int n);
 void kernel_spectrum(int nx, int ny, int nz, double dx, double dy, double dz, std::vector<float>& out);
 }  // namespace mmh
 
+// Parameters of a run, applied to an instance's control block at its start.
+struct MmRunArgs {
+  InstCtl* ctl;
+  double T, t_end_abs, tol, dt_fixed, dt_min, dt_max;   // t_end = t_end_abs if finite, t + T if T > 0, else unbounded
+  int rec_index, sampling, trace_on, pad;               // sampling: the trace settings below are new
+  double trace_dt;
+  long long trace_max, trace_stride;
+};
+// What a run leaves for the instance's statistics.
+struct MmRunStats {
+  long long accepted, rejected;
+  double t, dt, dt_fixed, dt_min_seen, dt_max_seen;
+  int status;
+};
+__host__ __device__ inline void mm_apply_run(InstCtl& h, const MmRunArgs& r) {
+  h.t_end = r.t_end_abs - r.t_end_abs == 0.0 ? r.t_end_abs : r.T > 0 ? h.t + r.T : 1e300;
+  h.tol = r.tol;
+  h.dt_fixed = r.dt_fixed;
+  h.dt_min = r.dt_min;
+  h.dt_max = r.dt_max;
+  h.done = 0;
+  h.status = 0;
+  // the run-start stage kernel evaluates the feedback from the stage
+  // amplitude: it must be the amplitude of the state the run starts from
+  // (a previous run leaves the next stage input there, mm_set_a and
+  // mm_set_state set a alone)
+  for (int n = 0; n < MMI_MAX_MODES; ++n) {
+    h.as[n][0] = h.a[n][0];
+    h.as[n][1] = h.a[n][1];
+  }
+  h.rec_index = r.rec_index;
+  if (r.sampling) {
+    h.trace_on = r.trace_on;
+    h.trace_started = 0;
+    h.trace_n = 0;
+    h.trace_steps = 0;
+    h.trace_max = r.trace_max;
+    h.trace_dt = r.trace_dt;
+    h.trace_stride = r.trace_stride;
+  }
+}
+// exchanges with the host through pinned memory, on the null stream (kernels_io.hip)
+hipError_t mmk_launch_state_out(const InstCtl* c, const float* y0, const float* y1, int n, char* dst);
+hipError_t mmk_launch_state_in(InstCtl* c, float* y0, int n, const char* src);
+hipError_t mmk_launch_trace_out(const InstCtl* c, const double* trace, long long cap, int N, long long most, double* dst);
+hipError_t mmk_launch_run_begin(const MmRunArgs* args, int count);
+hipError_t mmk_launch_run_stats(InstCtl* const* ctl, MmRunStats* out, int count);
+hipError_t mmk_launch_to_float(const double* src, float* dst, size_t n);
+
 hipError_t mmk_launch_xfwd_cells(int method, int stage, int nblocks, const InstDesc* descs, const int* wg,
                                  const float2* tw, size_t lds, hipStream_t s);
 hipError_t mmk_launch_stage(int method, int stage, bool final_pass, int nblocks, int count,
