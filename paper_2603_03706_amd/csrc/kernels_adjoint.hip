@@ -35,39 +35,29 @@
 
 namespace mmk {
 
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[wv] = v;
-  __syncthreads();
-  double r = sh[0];
-#pragma unroll
-  for (int w = 1; w < MMI_WG / 64; ++w) r += sh[w];
-  return r;
-}
-
-// K block sums with one exchange through LDS (sh: K * MMI_WG / 64 doubles);
-// every value is added in the same order as by block_sum.
-template <int K>
-__device__ __forceinline__ void block_sums(double (&v)[K], double* sh) {
-  constexpr int NW = MMI_WG / 64;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
-  __syncthreads();
-  if (lane == 0)
-#pragma unroll
-    for (int k = 0; k < K; ++k) sh[k * NW + wv] = v[k];
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double r = sh[k * NW];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) r += sh[k * NW + w];
-    v[k] = r;
+// The sums of stage kernel A over a workgroup.  Two values at a time go
+// through the butterfly of a wavefront (wave_sum2), the wave sums of up to four
+// modes meet in LDS, and one thread a sum adds them in wavefront order.  With
+// a butterfly for each of the 16 sums of a four-mode film and two barriers a
+// mode A took 28.4 us on 128x128x32 cells, 26.1 so; of its 140 bytes a cell 64
+// are the update of grad u in double.
+struct AdjSums {
+  static constexpr int MODES = 4, NW = MMI_WG / 64;
+  static constexpr int ROWS = 3 * MODES + 4;         // per mode fb, Re m^-, Im m^-; then alpha, B0
+  double* sh;
+  __device__ __forceinline__ void put2(int row0, int row1, double a, double b) const {
+    const double w = wave_sum2(a, b);
+    const int lane = threadIdx.x & 63;
+    if ((lane & 31) == 0) sh[(lane ? row1 : row0) * NW + (threadIdx.x >> 6)] = w;
   }
-}
+  // sum of row threadIdx.x
+  __device__ __forceinline__ double row() const {
+    double r = sh[threadIdx.x * NW];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) r += sh[threadIdx.x * NW + w];
+    return r;
+  }
+};
 
 __device__ __forceinline__ void cross3(const float* a, const float* b, float* o) {
   o[0] = a[1] * b[2] - a[2] * b[1];
@@ -88,11 +78,13 @@ __device__ __forceinline__ double adj_step(const InstDesc& D, CtlPtr C) {
 // It needs the partial sums of stage kernel A and nothing of stage kernel B,
 // which touches none of what it writes (but for the index of the recorded
 // step at the end of a DP45 step), so one workgroup per instance runs it
-// beside B's own in B's launch; the step start runs beside k_adj_start.  As
-// launches of their own, each slot summed by the whole workgroup in turn,
-// these took 27 us a stage on the 128x128x32 film (1024 records, four modes)
-// and 4 us and a launch on small grids: its reverse step 0.62 vs 0.74 ms, that
-// of the 8x8x1 geometry 38 vs 85 us.
+// beside B's own, ahead of them in B's launch; the step start runs beside
+// k_adj_start.  As launches of their own, each slot summed by the whole
+// workgroup in turn, these took 27 us a stage on the 128x128x32 film (1024
+// records, four modes) and 4 us and a launch on small grids: its reverse step
+// 0.62 vs 0.74 ms.  Behind B's workgroups and with the modes one after the
+// other in one lane (their mu_a in scratch memory, which the whole kernel then
+// carries) it was what B waited for: B of the film 28.5 vs 23.5 us.
 template <bool DP, int ST>
 __device__ void adj_cav(const InstDesc* __restrict__ descs, int inst, double* tot) {
   constexpr bool kStart = DP ? ST == 7 : ST == 5;
@@ -123,101 +115,91 @@ __device__ void adj_cav(const InstDesc* __restrict__ descs, int inst, double* to
     }
     __syncthreads();
   }
-  if (threadIdx.x != 0) return;
+  // then lane n of the first wavefront carries mode n
+  if (threadIdx.x >= 64) return;
+  const int n = threadIdx.x;
+  const bool mode = n < N;
   if (kStart) {
-    // a loss on the trace: its derivative at the end of the step being reversed
-    if (!DP && D.dla_trace) {
-      const double* q = D.dla_trace + (size_t)(C->adj_base + C->rec_index + 1) * N * 2;
-      for (int n = 0; n < N; ++n) {
-        C->la[n][0] += q[2 * n];
-        C->la[n][1] += q[2 * n + 1];
-      }
-    }
+    if (!mode) return;
     const double wl = DP ? h * DPCoef::b6 : h / 6.0;
-    for (int n = 0; n < N; ++n)
-      for (int r = 0; r < 2; ++r) {
-        C->lza[n][r] = C->la[n][r];
-        C->lka[n][r] = wl * C->la[n][r];
-      }
+    // a loss on the trace: its derivative at the end of the step being reversed
+    const double* q = !DP && D.dla_trace ? D.dla_trace + ((size_t)(C->adj_base + C->rec_index + 1) * N + n) * 2 : nullptr;
+    for (int r = 0; r < 2; ++r) {
+      if (q) C->la[n][r] += q[r];
+      C->lza[n][r] = C->la[n][r];
+      C->lka[n][r] = wl * C->la[n][r];
+    }
   } else {
-    const double* as = D.rec_a + ((size_t)C->rec_index * D.rec_nstg + (ST - 1)) * N * 2;
+    const int ri = C->rec_index;
+    if (n == 0) {
+      C->grad_alpha += tot[MMI_ASLOT_ALPHA];
+      for (int c = 0; c < 3; ++c) C->grad_B0[c] += tot[MMI_ASLOT_B0 + c];
+      if (ST == 1) C->rec_index = ri - 1;
+    }
+    if (!mode) return;
+    const double* as = D.rec_a + (((size_t)ri * D.rec_nstg + (ST - 1)) * N + n) * 2;
     const double scale = D.inv_ngeo / (double)D.S;
-    C->grad_alpha += tot[MMI_ASLOT_ALPHA];
-    for (int c = 0; c < 3; ++c) C->grad_B0[c] += tot[MMI_ASLOT_B0 + c];
     const double cst = (ST == 4) ? h : 0.5 * h;
     const double wprev = h * (ST == 2 ? 1.0 : 2.0) / 6.0;
-    // mu_a of every mode first: with direct mode coupling it reads the
-    // lambda_ka of all modes, which the update below overwrites
-    double mu[MMI_MAX_MODES][2];
-    for (int n = 0; n < N; ++n) {
-      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
-      const double lr = C->lka[n][0], li = C->lka[n][1];
-      const double fb = tot[MMI_ASLOT_FB + n];
-      const double mr = tot[MMI_ASLOT_MM + 2 * n] * scale, mi = tot[MMI_ASLOT_MM + 2 * n + 1] * scale;
-      // dF/dg = (s + i c) m^- ; feedback h0 = 2 g / gamma with Re[e^{-i Phi} a] = c ar + s ai
-      const double fr = s * mr - c * mi, fi = s * mi + c * mr;
-      C->grad_g[n] += lr * fr + li * fi + fb * (2.0 / D.gamma) * (c * as[2 * n] + s * as[2 * n + 1]);
-      // mu_a = conj(-kappa - i w) lambda_ka + h0 fb (c, s)
-      const double w = D.omega[n], kp = D.kappa[n];
-      double mur = -kp * lr - w * li + D.h0[n] * fb * c;
-      double mui = w * lr - kp * li + D.h0[n] * fb * s;
-      if (D.kerr_on) {
-        // transpose of the Jacobian of -i K |a|^2 a at the stage amplitude
-        const double ar = as[2 * n], ai = as[2 * n + 1], K = D.kerr[n];
-        const double q = K * (ar * ar + ai * ai), x = 2.0 * K * ar * ai;
-        mur += lr * x - li * (q + 2.0 * K * ar * ar);
-        mui += lr * (q + 2.0 * K * ai * ai) - li * x;
-      }
-      if (D.param_on) {
-        // transpose of the Jacobian of -i Lam conj(a), Lam = lam e^{-2 i wp t}
-        // at the stage time: [[Li, -Lr], [-Lr, -Li]] (symmetric)
-        const double ts = DP ? gbl(D.rec_t)[C->rec_index] + DPCoef::c(ST) * h
-                             : C->adj_t0 + (double)C->rec_index * h + (ST == 1 ? 0.0 : ST == 4 ? h : 0.5 * h);
-        double sn, cs;
-        sincos(2.0 * D.par_wp[n] * ts, &sn, &cs);
-        const double Lr = D.par_re[n] * cs + D.par_im[n] * sn;
-        const double Li = D.par_im[n] * cs - D.par_re[n] * sn;
-        mur += Li * lr - Lr * li;
-        mui -= Lr * lr + Li * li;
-      }
-      if (D.jcpl_on)
-        for (int q = 0; q < N; ++q) {
-          // -i sum_q J_qn a_n in the equation of mode q, J symmetric
-          mur -= D.jcpl[q][n] * C->lka[q][1];
-          mui += D.jcpl[q][n] * C->lka[q][0];
-        }
-      mu[n][0] = mur;
-      mu[n][1] = mui;
+    const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
+    const double lr = C->lka[n][0], li = C->lka[n][1];
+    const double ar = as[0], ai = as[1];
+    const double fb = tot[MMI_ASLOT_FB + n];
+    const double mr = tot[MMI_ASLOT_MM + 2 * n] * scale, mi = tot[MMI_ASLOT_MM + 2 * n + 1] * scale;
+    // dF/dg = (s + i c) m^- ; feedback h0 = 2 g / gamma with Re[e^{-i Phi} a] = c ar + s ai
+    const double fr = s * mr - c * mi, fi = s * mi + c * mr;
+    C->grad_g[n] += lr * fr + li * fi + fb * (2.0 / D.gamma) * (c * ar + s * ai);
+    // mu_a = conj(-kappa - i w) lambda_ka + h0 fb (c, s)
+    const double w = D.omega[n], kp = D.kappa[n];
+    double mu[2] = {-kp * lr - w * li + D.h0[n] * fb * c, w * lr - kp * li + D.h0[n] * fb * s};
+    if (D.kerr_on) {
+      // transpose of the Jacobian of -i K |a|^2 a at the stage amplitude
+      const double K = D.kerr[n];
+      const double q = K * (ar * ar + ai * ai), x = 2.0 * K * ar * ai;
+      mu[0] += lr * x - li * (q + 2.0 * K * ar * ar);
+      mu[1] += lr * (q + 2.0 * K * ai * ai) - li * x;
     }
-    for (int n = 0; n < N; ++n) {
-      C->la[n][0] += mu[n][0];
-      C->la[n][1] += mu[n][1];
+    if (D.param_on) {
+      // transpose of the Jacobian of -i Lam conj(a), Lam = lam e^{-2 i wp t}
+      // at the stage time: [[Li, -Lr], [-Lr, -Li]] (symmetric)
+      const double ts = DP ? gbl(D.rec_t)[ri] + DPCoef::c(ST) * h
+                           : C->adj_t0 + (double)ri * h + (ST == 1 ? 0.0 : ST == 4 ? h : 0.5 * h);
+      double sn, cs;
+      sincos(2.0 * D.par_wp[n] * ts, &sn, &cs);
+      const double Lr = D.par_re[n] * cs + D.par_im[n] * sn;
+      const double Li = D.par_im[n] * cs - D.par_re[n] * sn;
+      mu[0] += Li * lr - Lr * li;
+      mu[1] -= Lr * lr + Li * li;
+    }
+    if (D.jcpl_on)
+      // with direct mode coupling mu_a reads the lambda_ka of all modes (the
+      // stores below come after these loads for the whole wavefront)
+      for (int q = 0; q < N; ++q) {
+        // -i sum_q J_qn a_n in the equation of mode q, J symmetric
+        mu[0] -= D.jcpl[q][n] * C->lka[q][1];
+        mu[1] += D.jcpl[q][n] * C->lka[q][0];
+      }
+    __builtin_amdgcn_wave_barrier();
+    for (int r = 0; r < 2; ++r) {
+      C->la[n][r] += mu[r];
       if (!DP) {
-        if (ST > 1) {
-          C->lka[n][0] = wprev * C->lza[n][0] + cst * mu[n][0];
-          C->lka[n][1] = wprev * C->lza[n][1] + cst * mu[n][1];
-        }
+        if (ST > 1) C->lka[n][r] = wprev * C->lza[n][r] + cst * mu[r];
       } else if (ST > 1) {
         // lambda_ka(ST-1) = h (b_(ST-1) lambda_za + sum_{q>=ST} a_(q,ST-1) mu_a,q)
-        for (int r = 0; r < 2; ++r) {
-          if (ST >= 3) C->lmua[ST - 1][n][r] = mu[n][r];
-          double acc = DPCoef::b(ST - 1) * C->lza[n][r] + DPCoef::a(ST, ST - 1) * mu[n][r];
-          for (int q = ST + 1; q <= 6; ++q) acc += DPCoef::a(q, ST - 1) * C->lmua[q - 1][n][r];
-          C->lka[n][r] = h * acc;
-        }
+        if (ST >= 3) C->lmua[ST - 1][n][r] = mu[r];
+        double acc = DPCoef::b(ST - 1) * C->lza[n][r] + DPCoef::a(ST, ST - 1) * mu[r];
+        for (int q = ST + 1; q <= 6; ++q) acc += DPCoef::a(q, ST - 1) * C->lmua[q - 1][n][r];
+        C->lka[n][r] = h * acc;
       }
     }
-    if (ST == 1) C->rec_index -= 1;
   }
   // adjoint of m^- for the next stage kernel A: conj(i g e^{-i Phi}) lambda_ka
   if (ST >= 2) {
-    for (int n = 0; n < N; ++n) {
-      const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
-      const double lr = C->lka[n][0], li = C->lka[n][1];
-      // conj(g (s + i c)) = g (s - i c)
-      C->lmm[n][0] = g * (s * lr + c * li);
-      C->lmm[n][1] = g * (s * li - c * lr);
-    }
+    const double c = D.cphi[n], s = D.sphi[n], g = D.g[n];
+    const double lr = C->lka[n][0], li = C->lka[n][1];
+    // conj(g (s + i c)) = g (s - i c)
+    C->lmm[n][0] = g * (s * lr + c * li);
+    C->lmm[n][1] = g * (s * li - c * lr);
   }
 }
 
@@ -233,13 +215,14 @@ __global__ __launch_bounds__(MMI_WG) void k_adj_cav(const InstDesc* __restrict__
 // lambda_k4 = h/6 lambda_z.
 template <bool DP>
 __global__ __launch_bounds__(MMI_WG) void k_adj_start(const InstDesc* __restrict__ descs,
-                                                      const int* __restrict__ wg_inst, int nblocks) {
+                                                      const int* __restrict__ wg_inst, int nblocks, int count) {
   __shared__ double tot[MMI_PSTRIDE];
-  if ((int)blockIdx.x >= nblocks) {
-    adj_cav<DP, DP ? 7 : 5>(descs, (int)blockIdx.x - nblocks, tot);
+  const int lead = (int)gridDim.x - nblocks;
+  if ((int)blockIdx.x < lead) {
+    if ((int)blockIdx.x < count) adj_cav<DP, DP ? 7 : 5>(descs, blockIdx.x, tot);
     return;
   }
-  const int lblk = xcd_block(nblocks);
+  const int lblk = xcd_block(nblocks, lead);
   const InstDesc& D = descs[wg_inst[lblk]];
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) return;
@@ -281,7 +264,7 @@ template <int ST>
 __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k_adj_a(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
                                                   const float2* __restrict__ tw) {
-  __shared__ double sh[4 * (MMI_WG / 64)];
+  __shared__ double sh[AdjSums::ROWS * (MMI_WG / 64)];
   extern __shared__ float2 xl[];
   const int lblk = xcd_block();
   const InstDesc& D = descs[wg_inst[lblk]];
@@ -313,7 +296,7 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
   if (mag)
     for (int n = 0; n < N; ++n) {
       const float b = (float)(D.h0[n] * (D.cphi[n] * as[2 * n] + D.sphi[n] * as[2 * n + 1]));
-      fb = fmaf(b, D.profiled ? u_[(size_t)n * nc + i] : 1.f, fb);
+      fb = fmaf(b, D.profiled ? gat(u_ + (size_t)n * nc, i) : 1.f, fb);
     }
   const float gl = D.gl, al = D.alpha;
   const float dga = 2.f * al / (1.f + al * al);   // -d ln(gamma')/d alpha
@@ -329,7 +312,7 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
   if (bd_recorded && valid) {
     const MMG float* RB = gbl(D.rec_bd) + ((size_t)ri * D.rec_nstg + (ST - 1)) * (size_t)(3 * nc);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) bdv[c] = RB[c * nc + i];
+    for (int c = 0; c < 3; ++c) bdv[c] = gat(RB, c * nc + i);
   }
   if (mag) {
 #pragma unroll
@@ -339,7 +322,7 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
       field_at(D, src, i, x, yy, zz, m, s, fb, D.demag == 2, B, bdv, bd_recorded);
       const float* ms = m[s];
       float l[3];
-      for (int c = 0; c < 3; ++c) l[c] = gbl(D.lam_k)[(s * 3 + c) * nc + i];
+      for (int c = 0; c < 3; ++c) l[c] = gat(gbl(D.lam_k), (s * 3 + c) * nc + i);
       float P[3], Q[3], lm[3], t1[3], t2[3], t3[3], lB[3];
       cross3(ms, B, P);
       cross3(ms, P, Q);
@@ -361,7 +344,7 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
       gb0y += lB[1];
       gb0z += lB[2];
       lbx[s] = lB[0];
-      for (int c = 0; c < 3; ++c) lam_B[(s * 3 + c) * nc + i] = lB[c];
+      for (int c = 0; c < 3; ++c) gat(lam_B, (s * 3 + c) * nc + i) = lB[c];
       if (s == 0)
         for (int c = 0; c < 3; ++c) lb0[c] = lB[c];
     }
@@ -369,51 +352,60 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
     for (int s = 0; s < S; ++s)
       for (int c = 0; c < 3; ++c) lam_B[(s * 3 + c) * nc + i] = 0.f;
   }
-  // m^- transpose and the gradient of the mode profiles
-  for (int n = 0; n < N; ++n) {
-    const float u = D.profiled ? (valid ? u_[(size_t)n * nc + i] : 0.f) : 1.f;
-    const float lr = (float)C->lmm[n][0], li = (float)C->lmm[n][1];
-    double fbn = 0.0, mr = 0.0, mi = 0.0, gu = 0.0;
-    if (mag) {
-      const float arn = (float)as[2 * n], ain = (float)as[2 * n + 1];
-      const float fbw = (float)(D.h0[n] * (D.cphi[n] * arn + D.sphi[n] * ain));
+  // m^- transpose, the gradient of the mode profiles and the sums
+  const AdjSums sums{sh};
+  MMG double* const rec = gbl(D.partials) + (size_t)lw * MMI_PSTRIDE;
+  sums.put2(3 * AdjSums::MODES, 3 * AdjSums::MODES + 1, galpha, gb0x);
+  sums.put2(3 * AdjSums::MODES + 2, 3 * AdjSums::MODES + 3, gb0y, gb0z);
+  int n0 = 0;
+  do {
+    if (n0) __syncthreads();
+    double fbs[AdjSums::MODES] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        if (s >= S) continue;
-        const float cs = D.csign[s];
-        mux[s][0] += wmm * cs * u * lr;
-        mux[s][1] -= wmm * cs * u * li;
-        fbn += (double)(cs * lbx[s] * u);
-        mr += (double)(cs * m[s][0] * u);
-        mi -= (double)(cs * m[s][1] * u);
-        gu += (double)(cs * (lbx[s] * fbw + wmm * (lr * m[s][0] - li * m[s][1])));
+    for (int q = 0; q < AdjSums::MODES; ++q) {
+      const int n = n0 + q;
+      if (n >= N) break;
+      const float u = D.profiled ? (valid ? gat(u_ + (size_t)n * nc, i) : 0.f) : 1.f;
+      const float lr = (float)C->lmm[n][0], li = (float)C->lmm[n][1];
+      double fbn = 0.0, mr = 0.0, mi = 0.0, gu = 0.0;
+      if (mag) {
+        MMG double* const g = D.grad_u ? gbl(D.grad_u) + (size_t)n * nc : nullptr;
+        const double g0 = g ? gat(g, i) : 0.0;
+        const float arn = (float)as[2 * n], ain = (float)as[2 * n + 1];
+        const float fbw = (float)(D.h0[n] * (D.cphi[n] * arn + D.sphi[n] * ain));
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          if (s >= S) continue;
+          const float cs = D.csign[s];
+          mux[s][0] += wmm * cs * u * lr;
+          mux[s][1] -= wmm * cs * u * li;
+          fbn += (double)(cs * lbx[s] * u);
+          mr += (double)(cs * m[s][0] * u);
+          mi -= (double)(cs * m[s][1] * u);
+          gu += (double)(cs * (lbx[s] * fbw + wmm * (lr * m[s][0] - li * m[s][1])));
+        }
+        if (g) gat(g, i) = g0 + gu;
       }
-      if (D.grad_u) gbl(D.grad_u)[(size_t)n * nc + i] += gu;
+      fbs[q] = fbn;
+      sums.put2(3 * q + 1, 3 * q + 2, mr, mi);
+      if (q & 1) sums.put2(3 * (q - 1), 3 * q, fbs[q - 1], fbs[q]);
+      else if (n == N - 1) sums.put2(3 * q, 3 * q + 3, fbs[q], 0.0);   // (row 3 q + 3 is of no mode)
     }
-    double sums[3] = {fbn, mr, mi};
-    block_sums<3>(sums, sh);
-    if (threadIdx.x == 0) {
-      MMG double* rec = gbl(D.partials) + (size_t)lw * MMI_PSTRIDE;
-      rec[MMI_ASLOT_FB + n] = sums[0];
-      rec[MMI_ASLOT_MM + 2 * n] = sums[1];
-      rec[MMI_ASLOT_MM + 2 * n + 1] = sums[2];
+    __syncthreads();
+    const int k = threadIdx.x, q = k / 3, r = k - 3 * q;
+    if (k < 3 * AdjSums::MODES) {
+      if (n0 + q < N) rec[r == 0 ? MMI_ASLOT_FB + n0 + q : MMI_ASLOT_MM + 2 * (n0 + q) + r - 1] = sums.row();
+    } else if (n0 == 0 && k < AdjSums::ROWS) {
+      rec[MMI_ASLOT_ALPHA + k - 3 * AdjSums::MODES] = sums.row();
     }
-  }
+    n0 += AdjSums::MODES;
+  } while (n0 < N);
   if (valid)
 #pragma unroll
     for (int s = 0; s < 2; ++s)
       if (s < S)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) gbl(D.mu)[(s * 3 + c) * nc + i] = mux[s][c];
-  double r[4] = {galpha, gb0x, gb0y, gb0z};
-  block_sums<4>(r, sh);
-  if (threadIdx.x == 0) {
-    MMG double* rec = gbl(D.partials) + (size_t)lw * MMI_PSTRIDE;
-    rec[MMI_ASLOT_ALPHA] = r[0];
-    rec[MMI_ASLOT_B0] = r[1];
-    rec[MMI_ASLOT_B0 + 1] = r[2];
-    rec[MMI_ASLOT_B0 + 2] = r[3];
-  }
+        for (int c = 0; c < 3; ++c) gat(gbl(D.mu), (s * 3 + c) * nc + i) = mux[s][c];
   if (D.xfused) {
     // R2C of the field adjoint of this workgroup's x-rows: the X rows of its
     // convolution (no separate x-forward pass)
@@ -427,14 +419,15 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
 template <bool DP, int ST>
 __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(8), amdgpu_num_sgpr(80))) void k_adj_b(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
-                                                  const float2* __restrict__ tw, int nblocks) {
+                                                  const float2* __restrict__ tw, int nblocks, int count) {
   __shared__ double tot[MMI_PSTRIDE];
   extern __shared__ float2 xl[];
-  if ((int)blockIdx.x >= nblocks) {
-    adj_cav<DP, ST>(descs, (int)blockIdx.x - nblocks, tot);
+  const int lead = (int)gridDim.x - nblocks;
+  if ((int)blockIdx.x < lead) {
+    if ((int)blockIdx.x < count) adj_cav<DP, ST>(descs, blockIdx.x, tot);
     return;
   }
-  const int lblk = xcd_block(nblocks);
+  const int lblk = xcd_block(nblocks, lead);
   const InstDesc& D = descs[wg_inst[lblk]];
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) return;
@@ -451,77 +444,77 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(8), amdg
   const int i = wg_cell(D, lw);
   if (i >= nc) return;   // no barrier below
   const bool mag = !D.has_geom || gbl(D.geom)[i];
-  const int nx = D.nx, ny = D.ny, nz = D.nz;
-  int x, y, z;
-  cell_xyz(D, i, x, y, z);
-  const MMG float* L = gbl(D.lam_B);
-  const MMG uint8_t* G = D.has_geom ? gbl(D.geom) : nullptr;
+  const MMG float* const L = gbl(D.lam_B);
   MMG float* const lam_y = gbl(D.lam_y);
-  MMG float* const lam_z = gbl(D.lam_z);
+  const MMG float* const lam_z = gbl(D.lam_z);
+  const MMG float* const mu_ = gbl(D.mu);
   MMG float* const lam_k = gbl(D.lam_k);
-  constexpr bool dp = DP;
   const double h = adj_step(D, C);
   // RK4: coefficient of k_(ST-1) in y_ST and the weight of k_(ST-1)
   const float cst = (float)(ST == 4 ? h : 0.5 * h);
   const float wprev = (float)(h * (ST == 2 ? 1.0 : 2.0) / 6.0);
   // DP45: lambda_k(ST-1) = h (b_(ST-1) lambda_z + sum_{q>=ST} a_(q,ST-1) mu_q)
   const size_t vec = (size_t)3 * S * nc;
+  int x, y, z, jn[6];
+  cell_xyz(D, i, x, y, z);
+  neighbours(D, i, x, y, z, jn);
+  const float cq[6] = {D.cex_x, D.cex_x, D.cex_y, D.cex_y, D.cex_z, D.cex_z};
+  const float e[3] = {D.ex, D.ey, D.ez}, nl[3] = {D.nlx, D.nly, D.nlz};
+  const bool bd_sep = D.demag == 2 && !D.xfused;
+  // own field adjoints of both sublattices (they couple through local demag
+  // and B_E)
   float lb[2][3] = {{0.f, 0.f, 0.f}, {0.f, 0.f, 0.f}};
-  for (int s = 0; s < S; ++s)
-    for (int c = 0; c < 3; ++c) lb[s][c] = L[(s * 3 + c) * nc + i];
-  for (int s = 0; s < S; ++s) {
-    float mu[3];
-    for (int c = 0; c < 3; ++c) mu[c] = gbl(D.mu)[(s * 3 + c) * nc + i];
-    if (mag) {
-      // exchange (a symmetric graph Laplacian over magnetic pairs)
-      const int base = s * 3 * nc;
-      float ex[3] = {0.f, 0.f, 0.f};
-#define MM_NBR(cond, off, coef)                                       \
-  if (cond) {                                                         \
-    const int j = i + (off);                                          \
-    if (!G || G[j]) {                                                 \
-      for (int c = 0; c < 3; ++c)                                     \
-        ex[c] = fmaf(coef, L[base + c * nc + j] - lb[s][c], ex[c]);   \
-    }                                                                 \
-  }
-      MM_NBR(x > 0, -1, D.cex_x)
-      MM_NBR(x < nx - 1, 1, D.cex_x)
-      MM_NBR(y > 0, -nx, D.cex_y)
-      MM_NBR(y < ny - 1, nx, D.cex_y)
-      MM_NBR(z > 0, -nx * ny, D.cex_z)
-      MM_NBR(z < nz - 1, nx * ny, D.cex_z)
-#undef MM_NBR
-      const float e[3] = {D.ex, D.ey, D.ez};
-      const float le = lb[s][0] * e[0] + lb[s][1] * e[1] + lb[s][2] * e[2];
-      const float nl[3] = {D.nlx, D.nly, D.nlz};
-      for (int c = 0; c < 3; ++c) {
-        float v = mu[c] + ex[c] + D.cK * le * e[c];
-        if (D.demag == 1) {
-          float t = lb[0][c];
-          if (S == 2) t += lb[1][c];
-          v += nl[c] * t;
-        } else if (D.demag == 2) {
-          v += D.xfused ? bdv[c] : gbl(D.bd)[c * nc + i];
-        }
-        if (S == 2) v -= D.BE * lb[1 - s][c];
-        mu[c] = v;
-      }
-    } else {
-      mu[0] = mu[1] = mu[2] = 0.f;
-    }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+    if (s < S)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) lb[s][c] = gat(L, (s * 3 + c) * nc + i);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    if (s >= S) continue;
+    // Every load before any store, so that they are in flight together, a
+    // neighbour that is absent replaced by the cell itself: with a branch per
+    // neighbour its loads were six round trips one after the other (128x128x32
+    // film: 31.5 vs 28.5 us; it moves about 65 MB).
+    float nb[6][3], mu[3], ly[3], lz[3], ms[4][3];
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
+      const int base = (s * 3 + c) * nc;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) nb[q][c] = gat(L, base + jn[q]);
+      mu[c] = gat(mu_, base + i);
+      ly[c] = gat(lam_y, base + i);
+      lz[c] = ST > 1 ? gat(lam_z, base + i) : 0.f;
+      if (bd_sep) bdv[c] = gat(gbl(D.bd), c * nc + i);
+#pragma unroll
+      for (int q = ST + 1; q <= 6; ++q)
+        if (DP && ST > 1) ms[q < 3 ? 0 : q - 3][c] = gat(gbl(D.mu_st) + (size_t)(q - 3) * vec, base + i);
+    }
+    // exchange (a symmetric graph Laplacian over magnetic pairs)
+    float ex[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) ex[c] = fmaf(cq[q], nb[q][c] - lb[s][c], ex[c]);
+    const float le = lb[s][0] * e[0] + lb[s][1] * e[1] + lb[s][2] * e[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float v = mu[c] + ex[c] + D.cK * le * e[c];
+      if (D.demag == 1) v += nl[c] * (S == 2 ? lb[0][c] + lb[1][c] : lb[0][c]);
+      else if (D.demag == 2) v += bdv[c];
+      if (S == 2) v -= D.BE * lb[1 - s][c];
+      v = mag ? v : 0.f;
       const int idx = (s * 3 + c) * nc + i;
-      lam_y[idx] += mu[c];
-      if (!dp) {
-        if (ST > 1) lam_k[idx] = fmaf(wprev, lam_z[idx], cst * mu[c]);
+      gat(lam_y, idx) = ly[c] + v;
+      if (!DP) {
+        if (ST > 1) gat(lam_k, idx) = fmaf(wprev, lz[c], cst * v);
       } else if (ST > 1) {
         // keep mu of stages 3..6 for the stages below
-        if (ST >= 3) gbl(D.mu_st)[(size_t)(ST - 3) * vec + idx] = mu[c];
-        float acc = (float)(DPCoef::b(ST - 1)) * lam_z[idx] + (float)DPCoef::a(ST, ST - 1) * mu[c];
+        if (ST >= 3) gat(gbl(D.mu_st) + (size_t)(ST - 3) * vec, idx) = v;
+        float acc = (float)(DPCoef::b(ST - 1)) * lz[c] + (float)DPCoef::a(ST, ST - 1) * v;
 #pragma unroll
-        for (int q = ST + 1; q <= 6; ++q)
-          acc = fmaf((float)DPCoef::a(q, ST - 1), gbl(D.mu_st)[(size_t)(q - 3) * vec + idx], acc);
-        lam_k[idx] = (float)h * acc;
+        for (int q = ST + 1; q <= 6; ++q) acc = fmaf((float)DPCoef::a(q, ST - 1), ms[q < 3 ? 0 : q - 3][c], acc);
+        gat(lam_k, idx) = (float)h * acc;
       }
     }
   }
@@ -535,9 +528,10 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(8), amdg
 // launch of its own (kind 3).
 hipError_t mmk_launch_adj(int kind, bool dp, int stage, int nblocks, int count, const InstDesc* d, const int* wg,
                           hipStream_t s, const float2* tw, size_t lds) {
+  const int lead = (count + 7) & ~7;   // whole rounds over the XCDs, so that the cells' workgroups keep theirs
   if (kind == 0) {
-    if (dp) MM_LAUNCH(mmk::k_adj_start<true>, dim3(nblocks + count), dim3(MMI_WG), 0, s, d, wg, nblocks);
-    else MM_LAUNCH(mmk::k_adj_start<false>, dim3(nblocks + count), dim3(MMI_WG), 0, s, d, wg, nblocks);
+    if (dp) MM_LAUNCH(mmk::k_adj_start<true>, dim3(lead + nblocks), dim3(MMI_WG), 0, s, d, wg, nblocks, count);
+    else MM_LAUNCH(mmk::k_adj_start<false>, dim3(lead + nblocks), dim3(MMI_WG), 0, s, d, wg, nblocks, count);
     return hipGetLastError();
   }
   if (kind == 3 && dp && stage == 1) {
@@ -551,8 +545,8 @@ hipError_t mmk_launch_adj(int kind, bool dp, int stage, int nblocks, int count, 
   }
 #define MM_ADJ_B(DP, ST)                                                                              \
   if (kind == 2 && dp == DP && stage == ST) {                                                         \
-    MM_LAUNCH((mmk::k_adj_b<DP, ST>), dim3(nblocks + (DP && ST == 1 ? 0 : count)), dim3(MMI_WG), lds, s, d, wg, tw, \
-              nblocks);                                                                               \
+    MM_LAUNCH((mmk::k_adj_b<DP, ST>), dim3((DP && ST == 1 ? 0 : lead) + nblocks), dim3(MMI_WG), lds, s, d, wg, tw, \
+              nblocks, count);                                                                        \
     return hipGetLastError();                                                                         \
   }
   MM_ADJ_A(1) MM_ADJ_A(2) MM_ADJ_A(3) MM_ADJ_A(4) MM_ADJ_A(5) MM_ADJ_A(6)

@@ -238,9 +238,9 @@ __device__ __forceinline__ float2 conv_row(const InstDesc& D, const MMG float2* 
 // that are neighbours in z, two 512-cell workgroups apart, are then read
 // through the same L2 instead of being fetched again by another XCD.
 // With nb given, it is the bijection on [0, nb) for launches that carry other
-// work in the blocks beyond.
-__device__ __forceinline__ int xcd_block(int nb) {
-  const int b = blockIdx.x;
+// work in the blocks beyond, or in `lead` blocks (a multiple of eight) before.
+__device__ __forceinline__ int xcd_block(int nb, int lead = 0) {
+  const int b = (int)blockIdx.x - lead;
   const int q = nb >> 3, r = nb & 7, x = b & 7;
   return x * q + min(x, r) + (b >> 3);
 }

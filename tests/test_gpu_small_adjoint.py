@@ -25,3 +25,17 @@ pytestmark = pytest.mark.gpu
 def test_small_reverse_steps_against_oracle(grid, kw):
     print("small reverse steps", grid, kw, flush=True)
     _check(_inst(grid, seed=sum(grid), **kw), steps=12, every=5, mode=0)
+
+
+@pytest.mark.parametrize("grid,kw", [
+    ((25, 41, 1), dict(modes=1)),                                    # one mode, uniform
+    ((25, 41, 1), dict(modes=3, profiled=True, coupled=True)),       # an odd mode in a group of four, mode coupling
+    ((43, 12, 2), dict(S=2, modes=4, profiled=True, mask=True)),     # 1032 cells, two sublattices, a full group
+    ((25, 41, 1), dict(modes=5, profiled=True)),                     # a second group of one mode
+    ((43, 25, 1), dict(modes=16, profiled=True, mask=True)),         # 1075, the most modes
+])
+def test_per_stage_reverse_sums_against_oracle(grid, kw):
+    """The sums of the per-stage kernels, four modes at a time, on instances
+    too large for the kernel above."""
+    print("per-stage reverse steps", grid, kw, flush=True)
+    _check(_inst(grid, seed=sum(grid), **kw), steps=6, every=4, mode=0)
