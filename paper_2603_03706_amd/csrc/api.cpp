@@ -1199,32 +1199,53 @@ mm_status enqueue_start(mm_batch* b) {
 // already in X (written by the previous stage kernel) except the DP45 stage
 // 2 input, which depends on the step size chosen after stage 7.
 // With FFT demag, the finalisation of a stage other than the last of the step
-// runs as extra workgroups of the next stage's first y-z (or y-forward)
+// (see below for that one) runs as extra workgroups of the next stage's first y-z (or y-forward)
 // launch: the transform reads and writes only X (and Y), which the
 // finalisation does not touch, and the next stage kernel comes after both in
 // stream order.
 bool merge_final(const mm_batch* b) { return !b->groups.empty(); }
 
-mm_status enqueue_step(mm_batch* b) {
+// Whether the finalisation of an RK4 step's last stage may do the same in the
+// next step: it moves the state on, which x-forward kernels read, so every
+// group has to have its x passes in the stage kernels (whose last one wrote
+// the X rows of the new state).  A DP45 step's last one chooses the step size
+// that its next stage input needs.  100x60x20 RK4 step: 131 us with a launch
+// of its own (6.9 us), 124 so.
+bool merge_step_end(const mm_batch* b) {
+  if (b->method != MM_RK4 || !merge_final(b)) return false;
+  for (const auto& g : b->groups)
+    if (!g.xfused) return false;
+  return true;
+}
+
+// `pending`: the stage whose finalisation this step's first transform carries
+// (-1: none), and on return the one left to the next step; the last step of a
+// launch sequence leaves none.
+mm_status enqueue_step(mm_batch* b, int& pending, bool last) {
   if (!b->gen_wg) return MM_OK;
   const int s0 = b->method == MM_RK4 ? 1 : 2;
   const int s1 = b->method == MM_RK4 ? 4 : 7;
-  int pending = -1;
   for (int st = s0; st <= s1; ++st) {
     const bool fwd = b->method == MM_DP45 && st == 2;
     if (mm_status s = enqueue_demag(b, st, -1, fwd, false, pending)) return s;
-    const bool merge = st < s1 && merge_final(b);
+    const bool merge = st < s1 ? merge_final(b) : !last && merge_step_end(b);
     if (mm_status s = enqueue_stage(b, st, !merge)) return s;
     pending = merge ? st : -1;
   }
   return MM_OK;
 }
 
+mm_status enqueue_steps(mm_batch* b, int steps) {
+  int pending = -1;
+  for (int k = 0; k < steps; ++k)
+    if (mm_status s = enqueue_step(b, pending, k == steps - 1)) return s;
+  return MM_OK;
+}
+
 // Capture `steps` consecutive steps of the batch into one executable graph.
 mm_status capture_steps(mm_batch* b, int steps, hipGraph_t* graph, hipGraphExec_t* exec) {
   MM_HIP(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-  mm_status st = MM_OK;
-  for (int k = 0; k < steps && st == MM_OK; ++k) st = enqueue_step(b);
+  const mm_status st = enqueue_steps(b, steps);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(b->stream, &g);
   if (st != MM_OK) {
@@ -2072,8 +2093,7 @@ mm_status mm_run_noalloc(mm_ctx* c, double T, double tol) {
   MM_HIP(mmk_launch_fill_zero(b.rb.lo, b.rb.bytes, b.stream));
   if (mm_status s = begin_run(&b, T, tol)) return s;
   for (;;) {
-    for (int k = 0; k < kStepsPerGraph; ++k)
-      if (mm_status s = enqueue_step(&b)) return s;
+    if (mm_status s = enqueue_steps(&b, kStepsPerGraph)) return s;
     if (mm_status s = enqueue_small(&b, b.gen_wg ? kStepsPerGraph : kSmallSteps)) return s;
     MM_HIP(mmk_launch_gather_done(1, b.d_desc, b.d_flags, b.stream));
     MM_HIP(hipMemcpyAsync(b.h_flags, b.d_flags, sizeof(int) * 2, hipMemcpyDeviceToHost, b.stream));
@@ -2806,7 +2826,7 @@ mm_status mm_batch_profile(mm_batch* b, int64_t steps, double tol, int32_t cap, 
   b->profiling = true;
   mm_status st = MM_OK;
   for (int64_t k = 0; k < steps && st == MM_OK; ++k) {
-    st = enqueue_step(b);
+    st = enqueue_steps(b, 1);
     if (st == MM_OK) st = enqueue_small(b, 1);
   }
   b->profiling = false;
