@@ -142,8 +142,11 @@ def profile_name(kernel):
     if m:
         return f"{m.group(1)}_{'rk4' if m.group(2) == '0' else 'dp45'}_{m.group(3)}" \
             if not (m.group(1) == "stage" and m.group(2) == "0" and m.group(3) == "0") else "stage_rk4_start"
-    if k.startswith(("mmk::k_fft_yzr<", "mmk::k_fft_yz8<", "mmk::k_fft_yzx<")):
+    if k.startswith(("mmk::k_fft_yzr<", "mmk::k_fft_yz8<", "mmk::k_fft_yzx<", "mmk::k_fft_yzh<", "mmk::k_fft_yzs<",
+                     "mmk::k_fft_y1<")):
         return "fft_yz_convolve"
+    if k.startswith(("mmk::k_small_rk4<", "mmk::k_small_adj<")):
+        return k[len("mmk::k_"):].split("<")[0]
     m = re.match(r"mmk::k_fft_ysx<\d+, (-?\d+)>", k)
     if m:
         return "fft_y_forward" if m.group(1) == "-1" else "fft_y_inverse"
