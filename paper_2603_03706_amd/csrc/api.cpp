@@ -1039,7 +1039,6 @@ bool any_xfused(const mm_batch* b) {
 mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true, bool inv = true,
                         int final_st = -1) {
   if (method < 0) method = b->method;
-  const int nfinal = final_st >= 0 ? (int)b->ctxs.size() : 0;
   // x-forward of the instances whose x passes run in the stage kernels: one
   // launch on the stage grid (forward stepping; the adjoint's inputs go
   // through the x kernels of their groups)
@@ -1051,7 +1050,8 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
         }))
       return s;
   for (auto& g : b->groups) {
-    const bool first = &g == &b->groups[0];
+    const int rides = &g == &b->groups[0] ? final_st : -1;
+    const int nfinal = rides >= 0 ? (int)b->ctxs.size() : 0;
     if (!g.xfused || (fwd && !cells_fwd))
     if (mm_status s = launch(b, "fft_x_forward", [&] {
           if (g.Wx == 0)
@@ -1062,33 +1062,32 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
     if (g.path == PATH_HALVES || g.path == PATH_SHORT) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
             auto f = g.path == PATH_HALVES ? mmk_launch_fft_yzh : mmk_launch_fft_yzs;
-            return f(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
-                                      first ? nfinal : 0, b->method, final_st);
+            return f(g.py, g.pz, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream, nfinal, b->method, rides);
           }))
         return s;
     } else if (g.path == PATH_REG8 || g.path == PATH_XCH) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
             auto f = g.path == PATH_XCH ? mmk_launch_fft_yzx : mmk_launch_fft_yz8;
             return f(g.py / 4, g.pz / 4, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
-                     first ? nfinal : 0, b->method, final_st);
+                     nfinal, b->method, rides);
           }))
         return s;
     } else if (g.path == PATH_REG) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
             return mmk_launch_fft_yzr(g.py / 4, g.pz / 4, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
-                                      first ? nfinal : 0, b->method, final_st);
+                                      nfinal, b->method, rides);
           }))
         return s;
     } else if (g.path == PATH_FUSED) {
       if (mm_status s = launch(b, "fft_yz_convolve", [&] {
             return mmk_launch_fft_yz(g.TK, g.n_yz, g.lds_yz, b->d_desc, g.yz, g_twiddle, b->stream,
-                                     first ? nfinal : 0, b->method, final_st);
+                                     nfinal, b->method, rides);
           }))
         return s;
     } else if (g.path == PATH_SPLITX) {
       if (mm_status s = launch(b, "fft_y_forward", [&] {
             return mmk_launch_fft_ysx(-1, g.py, g.n_y, g.lds_y, b->d_desc, g.y, g_twiddle, b->stream,
-                                      first ? nfinal : 0, b->method, final_st);
+                                      nfinal, b->method, rides);
           }))
         return s;
       if (mm_status s = launch(b, "fft_z_convolve", [&] {
@@ -1102,7 +1101,7 @@ mm_status enqueue_demag(mm_batch* b, int stage, int method = -1, bool fwd = true
     } else {
       if (mm_status s = launch(b, "fft_y_forward", [&] {
             return mmk_launch_fft_y(-1, g.Wy, g.n_y, g.lds_y, b->d_desc, g.y, g_twiddle, b->stream,
-                                    first ? nfinal : 0, b->method, final_st);
+                                    nfinal, b->method, rides);
           }))
         return s;
       if (mm_status s = launch(b, "fft_z_convolve", [&] {
@@ -1201,8 +1200,10 @@ mm_status enqueue_start(mm_batch* b) {
 // With FFT demag, the finalisation of a stage other than the last of the step
 // (see below for that one) runs as extra workgroups of the next stage's first y-z (or y-forward)
 // launch: the transform reads and writes only X (and Y), which the
-// finalisation does not touch, and the next stage kernel comes after both in
-// stream order.
+// finalisation does not touch, and of the control block the flag that says
+// whether the run is over, which is one that no finalisation in the launch
+// sets (transform_idle); the next stage kernel comes after both in stream
+// order.
 bool merge_final(const mm_batch* b) { return !b->groups.empty(); }
 
 // Whether the finalisation of an RK4 step's last stage may do the same in the

@@ -33,6 +33,7 @@ __host__ __device__ inline void mm_apply_run(InstCtl& h, const MmRunArgs& r) {
   h.dt_min = r.dt_min;
   h.dt_max = r.dt_max;
   h.done = 0;
+  h.idle = 0;
   h.status = 0;
   // the run-start stage kernel evaluates the feedback from the stage
   // amplitude: it must be the amplitude of the state the run starts from
