@@ -492,6 +492,7 @@ struct mm_batch {
     int nx, ny, nz, px, py, pz, kx;
     int path;
     bool xfused = false;   // x passes inside the stage kernels
+    bool rides = true;     // finalisations may ride on the first y-z (or y-forward) launch
     int Wx, Wy, TW, TK = 1;
     WorkItem *xf = nullptr, *yz = nullptr, *y = nullptr, *zc = nullptr;
     int n_xf = 0, n_yz = 0, n_y = 0, n_zc = 0;
@@ -815,6 +816,10 @@ mm_status build_group(mm_batch::Group& g, DevArena* arena = nullptr) {
   // (room for the sums of a finalisation riding on the launch)
   g.lds_yz = std::max(g.lds_yz, sizeof(double) * MMI_PSTRIDE);
   g.lds_y = std::max(g.lds_y, sizeof(double) * MMI_PSTRIDE);
+  g.rides = g.path == PATH_FUSED   ? mmk_final_rides(MMK_RIDE_FUSED, g.py, g.pz, g.n_yz, g.lds_yz, g_cus)
+            : g.path == PATH_REG   ? mmk_final_rides(MMK_RIDE_REGISTER, g.py, g.pz, g.n_yz, g.lds_yz, g_cus)
+            : g.path == PATH_SPLIT ? mmk_final_rides(MMK_RIDE_Y, g.py, g.pz, g.n_y, g.lds_y, g_cus)
+                                   : true;
   return MM_OK;
 }
 
@@ -1197,14 +1202,14 @@ mm_status enqueue_start(mm_batch* b) {
 // One step.  Where the stage kernels do the x passes, each stage's input is
 // already in X (written by the previous stage kernel) except the DP45 stage
 // 2 input, which depends on the step size chosen after stage 7.
-// With FFT demag, the finalisation of a stage other than the last of the step
+// With FFT demag and a launch that can carry it (mmk_final_rides), the finalisation of a stage other than the last of the step
 // (see below for that one) runs as extra workgroups of the next stage's first y-z (or y-forward)
 // launch: the transform reads and writes only X (and Y), which the
 // finalisation does not touch, and of the control block the flag that says
 // whether the run is over, which is one that no finalisation in the launch
 // sets (transform_idle); the next stage kernel comes after both in stream
 // order.
-bool merge_final(const mm_batch* b) { return !b->groups.empty(); }
+bool merge_final(const mm_batch* b) { return !b->groups.empty() && b->groups[0].rides; }
 
 // Whether the finalisation of an RK4 step's last stage may do the same in the
 // next step: it moves the state on, which x-forward kernels read, so every

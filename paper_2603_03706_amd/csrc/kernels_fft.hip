@@ -216,13 +216,17 @@ __global__ __launch_bounds__(256) void k_fft_xi(const InstDesc* __restrict__ des
 // starts from nz nonzero rows: its first DIF stage (span Pz/2, upper half
 // zero) is folded into the copy into the tile, and the last DIT stage is
 // folded into the copy back, which keeps only z < nz.
+// FINAL: the form that carries finalisations in the workgroups beyond nwork.
+// They take 86 vector registers where the transform takes 23, which leaves two
+// workgroups to a CU instead of four; see mmk_final_rides.
 #define MM_YZ_T 512
+template <bool FINAL>
 __global__ __launch_bounds__(MM_YZ_T) void k_fft_yz(const InstDesc* __restrict__ descs,
                                                     const WorkItem* __restrict__ work,
                                                     const float2* __restrict__ tw, int TK, int nwork, int fmethod,
                                                     int fstage) {
   extern __shared__ float2 lds[];
-  if ((int)blockIdx.x >= nwork) {
+  if (FINAL && (int)blockIdx.x >= nwork) {
     final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
     return;
   }
@@ -412,7 +416,7 @@ __device__ __forceinline__ float2 fold_c(float2 x0, float2 x1, Root4 c, float2 w
   return cmul(s, w);
 }
 
-template <int MY, int MZ>
+template <int MY, int MZ, bool FINAL>
 __global__ __launch_bounds__(MM_YZR_T, 2) void k_fft_yzr(const InstDesc* __restrict__ descs,
                                                          const WorkItem* __restrict__ work,
                                                          const float2* __restrict__ tw, int nwork, int fmethod,
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(MM_YZR_T, 2) void k_fft_yzr(const InstDesc* __restr
   constexpr int PY = 4 * MY, PZ = 4 * MZ, RS = PY + 1, ZR = 2 * MZ, YR = 2 * MY;
   constexpr int lgMY = ilog2c(MY), lgMZ = ilog2c(MZ), lgPY = lgMY + 2;
   extern __shared__ float2 lds[];
-  if ((int)blockIdx.x >= nwork) {
+  if (FINAL && (int)blockIdx.x >= nwork) {
     final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
     return;
   }
@@ -1607,12 +1611,12 @@ __global__ __launch_bounds__(MM_XR_T) void k_fft_xir(const InstDesc* __restrict_
 
 // --------------------------------------------------------- split y passes
 // work item = tile of W lines (kx, c, z) of one instance; LDS [Py][W]
-template <int DIR>
+template <int DIR, bool FINAL>
 __global__ __launch_bounds__(256) void k_fft_y(const InstDesc* __restrict__ descs,
                                                const WorkItem* __restrict__ work, int W,
                                                const float2* __restrict__ tw, int nwork, int fmethod, int fstage) {
   extern __shared__ float2 lds[];
-  if ((int)blockIdx.x >= nwork) {
+  if (FINAL && (int)blockIdx.x >= nwork) {
     final_any(fmethod, fstage, descs, (int)blockIdx.x - nwork, reinterpret_cast<double*>(lds));
     return;
   }
@@ -1837,23 +1841,51 @@ hipError_t mmk_launch_fft_xi(int W, int nblocks, size_t lds, const InstDesc* d, 
 hipError_t mmk_launch_fft_yz(int TK, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
                              const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
   if (nfinal < 0 || (nfinal > 0 && lds < MMI_PSTRIDE * sizeof(double))) return hipErrorInvalidValue;
-  MM_LAUNCH(mmk::k_fft_yz, dim3(nblocks + nfinal), dim3(MM_YZ_T), lds, s, d, w, tw, TK, nblocks, fmethod, fstage);
+  if (nfinal) MM_LAUNCH(mmk::k_fft_yz<true>, dim3(nblocks + nfinal), dim3(MM_YZ_T), lds, s, d, w, tw, TK, nblocks, fmethod, fstage);
+  else MM_LAUNCH(mmk::k_fft_yz<false>, dim3(nblocks), dim3(MM_YZ_T), lds, s, d, w, tw, TK, nblocks, 0, 0);
   return hipGetLastError();
 }
 
 #define MM_YZR_CASE(A, B)                                                                        \
   if (MY == A && MZ == B) {                                                                      \
-    MM_LAUNCH((mmk::k_fft_yzr<A, B>), dim3(nblocks + nfinal), dim3(MM_YZR_T), lds, s, d, w, tw, nblocks, fmethod, \
-              fstage);                                                                           \
+    if (nfinal)                                                                                  \
+      MM_LAUNCH((mmk::k_fft_yzr<A, B, true>), dim3(nblocks + nfinal), dim3(MM_YZR_T), lds, s, d, w, tw, nblocks, fmethod, \
+                fstage);                                                                         \
+    else                                                                                         \
+      MM_LAUNCH((mmk::k_fft_yzr<A, B, false>), dim3(nblocks), dim3(MM_YZR_T), lds, s, d, w, tw, nblocks, 0, 0); \
     return hipGetLastError();                                                                    \
   }
+#define MM_YZR_EACH(F)                                                                    \
+  F(4, 4) F(8, 4) F(16, 4) F(32, 4) F(4, 8) F(8, 8) F(16, 8) F(32, 8) F(4, 16) F(8, 16) F(16, 16) F(32, 16)
 hipError_t mmk_launch_fft_yzr(int MY, int MZ, int nblocks, size_t lds, const InstDesc* d,
                               const WorkItem* w, const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
   if (nfinal < 0 || (nfinal > 0 && lds < MMI_PSTRIDE * sizeof(double))) return hipErrorInvalidValue;
-  MM_YZR_CASE(4, 4) MM_YZR_CASE(8, 4) MM_YZR_CASE(16, 4) MM_YZR_CASE(32, 4)
-  MM_YZR_CASE(4, 8) MM_YZR_CASE(8, 8) MM_YZR_CASE(16, 8) MM_YZR_CASE(32, 8)
-  MM_YZR_CASE(4, 16) MM_YZR_CASE(8, 16) MM_YZR_CASE(16, 16) MM_YZR_CASE(32, 16)
+  MM_YZR_EACH(MM_YZR_CASE)
   return hipErrorInvalidValue;
+}
+
+namespace {
+// workgroups of the launch in flight at once on a device of `cus` CUs
+int in_flight(const void* f, int threads, size_t lds, int nblocks, int cus) {
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, threads, lds) != hipSuccess) return 0;
+  return n * cus < nblocks ? n * cus : nblocks;
+}
+}  // namespace
+// The finalisation's registers cost these kernels workgroups in flight, which a
+// launch of more of them than that pays for in rounds: 200 x 2 rows at nx = 64,
+// eight instances (520 planes), 671 us per DP45 step riding and 472 with
+// launches of their own; one instance (65 planes) 344 and 362.
+bool mmk_final_rides(int kind, int py, int pz, int nblocks, size_t lds, int cus) {
+  auto same = [&](const void* with, const void* without, int threads) {
+    return in_flight(with, threads, lds, nblocks, cus) >= in_flight(without, threads, lds, nblocks, cus);
+  };
+  if (kind == MMK_RIDE_FUSED) return same((const void*)mmk::k_fft_yz<true>, (const void*)mmk::k_fft_yz<false>, MM_YZ_T);
+  if (kind == MMK_RIDE_Y) return same((const void*)mmk::k_fft_y<-1, true>, (const void*)mmk::k_fft_y<-1, false>, 256);
+#define MM_YZR_RIDES(A, B) \
+  if (py == 4 * A && pz == 4 * B) return same((const void*)mmk::k_fft_yzr<A, B, true>, (const void*)mmk::k_fft_yzr<A, B, false>, MM_YZR_T);
+  MM_YZR_EACH(MM_YZR_RIDES)
+  return false;
 }
 
 hipError_t mmk_launch_fft_xr(int dir, int MX, int nblocks, const InstDesc* d, const WorkItem* w, int method,
@@ -1957,8 +1989,9 @@ int mmk_sx_rows(int py) {
 hipError_t mmk_launch_fft_y(int dir, int W, int nblocks, size_t lds, const InstDesc* d,
                             const WorkItem* w, const float2* tw, hipStream_t s, int nfinal, int fmethod, int fstage) {
   if (nfinal < 0 || (nfinal > 0 && (dir > 0 || lds < MMI_PSTRIDE * sizeof(double)))) return hipErrorInvalidValue;
-  if (dir < 0) MM_LAUNCH(mmk::k_fft_y<-1>, dim3(nblocks + nfinal), dim3(256), lds, s, d, w, W, tw, nblocks, fmethod, fstage);
-  else MM_LAUNCH(mmk::k_fft_y<1>, dim3(nblocks), dim3(256), lds, s, d, w, W, tw, nblocks, 0, 0);
+  if (nfinal) MM_LAUNCH((mmk::k_fft_y<-1, true>), dim3(nblocks + nfinal), dim3(256), lds, s, d, w, W, tw, nblocks, fmethod, fstage);
+  else if (dir < 0) MM_LAUNCH((mmk::k_fft_y<-1, false>), dim3(nblocks), dim3(256), lds, s, d, w, W, tw, nblocks, 0, 0);
+  else MM_LAUNCH((mmk::k_fft_y<1, false>), dim3(nblocks), dim3(256), lds, s, d, w, W, tw, nblocks, 0, 0);
   return hipGetLastError();
 }
 
@@ -1969,15 +2002,18 @@ hipError_t mmk_launch_fft_zc(int TW, int nblocks, size_t lds, const InstDesc* d,
 }
 
 hipError_t mmk_set_lds_limits() {
-  hipError_t e = hipFuncSetAttribute((const void*)mmk::k_fft_yz,
+  hipError_t e = hipFuncSetAttribute((const void*)mmk::k_fft_yz<true>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)mmk::k_fft_yz<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
 #define MM_YZR_ATTR(A, B)                                                                         \
   if (e == hipSuccess)                                                                            \
-    e = hipFuncSetAttribute((const void*)mmk::k_fft_yzr<A, B>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+    e = hipFuncSetAttribute((const void*)mmk::k_fft_yzr<A, B, true>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                            160 * 1024);                                                          \
+  if (e == hipSuccess)                                                                            \
+    e = hipFuncSetAttribute((const void*)mmk::k_fft_yzr<A, B, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
                             160 * 1024);
-  MM_YZR_ATTR(4, 4) MM_YZR_ATTR(8, 4) MM_YZR_ATTR(16, 4) MM_YZR_ATTR(32, 4)
-  MM_YZR_ATTR(4, 8) MM_YZR_ATTR(8, 8) MM_YZR_ATTR(16, 8) MM_YZR_ATTR(32, 8)
-  MM_YZR_ATTR(4, 16) MM_YZR_ATTR(8, 16) MM_YZR_ATTR(16, 16) MM_YZR_ATTR(32, 16)
+  MM_YZR_EACH(MM_YZR_ATTR)
 #define MM_YZ8_ATTR(A, B)                                                                         \
   if (e == hipSuccess)                                                                            \
     e = hipFuncSetAttribute((const void*)mmk::k_fft_yz8<A, B>, hipFuncAttributeMaxDynamicSharedMemorySize, \

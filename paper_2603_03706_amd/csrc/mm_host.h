@@ -124,6 +124,10 @@ hipError_t mmk_launch_fft_y(int dir, int W, int nblocks, size_t lds, const InstD
                             int fstage = 0);
 hipError_t mmk_launch_fft_zc(int TW, int nblocks, size_t lds, const InstDesc* d, const WorkItem* w,
                              const float2* tw, hipStream_t s);
+// Whether finalisations ride on a launch of the fused or the register y-z kernel or of the split y forward pass
+// (nblocks workgroups, lds bytes each, on a device of cus CUs): where it keeps as many workgroups in flight with them as without
+enum { MMK_RIDE_FUSED, MMK_RIDE_REGISTER, MMK_RIDE_Y };
+bool mmk_final_rides(int kind, int py, int pz, int nblocks, size_t lds, int cus);
 hipError_t mmk_set_lds_limits();
 hipError_t mmk_launch_adj(int kind, bool dp, int stage, int nblocks, int count, const InstDesc* d, const int* wg,
                           hipStream_t s, const float2* tw = nullptr, size_t lds = 0);

@@ -64,3 +64,29 @@ def test_instances_that_end_at_different_steps(grids):
         c.run(4.9e-12)
         assert n == c.stats()["accepted"]
         assert np.array_equal(c.get_m(), m) and np.array_equal(c.get_a(), a)
+
+
+@pytest.mark.gpu
+def test_finalisations_ride_where_they_cost_no_workgroups():
+    """The fused y-z kernel holds fewer workgroups to a CU in the form that
+    carries finalisations: one instance's 65 planes are in flight at once all
+    the same, and eight instances' 520 only without.  An instance's results do
+    not depend on which of the two it is in."""
+    from paper_2603_03706_amd import mmcav, workloads as W
+    from tests.helpers import gpu_for
+    grid = (64, 200, 2)
+    insts = [W.Instance(grid=grid, cell=(5e-9,) * 3, Ms=140e3, Aex=3.65e-12, alpha=0.01, B0=(0.01, 0.0, 0.2 + 0.01 * k),
+                        demag=W.DEMAG_FFT, omega=np.array([3e10]), kappa=np.array([1e7]), g=np.array([3e8]),
+                        m0=W.tilted(grid, 10.0, 0.3), a0=np.array([0.05 + 0.02j]), method="dp45", dt0=0.2e-12)
+             for k in range(8)]
+    launches, got = [], []
+    for n in (1, 8):
+        print("riding", n, flush=True)
+        ctxs = [gpu_for(i) for i in insts[:n]]
+        b = mmcav.Batch(ctxs)
+        b.run(4e-12, 1e-5)
+        got.append((ctxs[0].get_m(), ctxs[0].get_a()))
+        launches.append({p["name"] for p in b.profile(2, 1e-5)})
+        b.close()
+    assert "final_dp45_2" not in launches[0] and "final_dp45_2" in launches[1]
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
