@@ -207,9 +207,14 @@ mm_status mm_run(mm_ctx* ctx, double T, double tol);
  * (mm_set_stream; the null stream if none) and waits for the run.  The
  * context must be set up (mm_set_modes and mm_set_m, which allocate its
  * state).  MM_ERR_ARG if the instance's scratch exceeds the array (about
- * 108 B per cell and sublattice plus, with FFT demag, 12 B per cell and the
- * x-transformed rows: e.g. a 64^3 grid with FFT demag fits, a 128x128x32 one
- * does not).  The array is cleared where it must start at zero at every
+ * 110 B per cell and sublattice plus, with FFT demag, the x-transformed rows
+ * of 24 (Px/2 + 1) ny nz bytes, three times that with the halved strategy,
+ * with the split ones the padded spectra beside them, and 12 B per cell where
+ * the x passes are kernels of their own: e.g. a 64^3 grid with FFT demag fits,
+ * a 128x128x32 one does not).  With padded y-z of
+ * 128 x 64 an instance that would exceed the array only with the halved
+ * strategy has the exchange strategy as its default, in every kind of run.
+ * The array is cleared where it must start at zero at every
  * call.  Runs of one process on one GPU share its array and are serialised
  * by a lock; runs on one GPU that overlap from two processes each have their
  * own array. */
@@ -304,7 +309,8 @@ mm_status mm_batch_tune_fft(mm_batch* b, char* report, size_t report_len);
 
 /* Demag y-z strategy for every FFT grid shape in the batch (mm_batch_tune
  * chooses one per shape by timing; before that the shape alone decides: the
- * halved strategy for padded y of 256 and for 128 x 64, else the first of
+ * halved strategy for padded y of 256 and for 128 x 64 (there for grids that
+ * mm_run_noalloc can take with it), else the first of
  * exchange, short, eight-lane register, register and fused that applies, else
  * the split exchange one, else the split one):
  *   MM_YZ_FUSED     y and z lines transformed in LDS by one workgroup per

@@ -866,14 +866,12 @@ mm_status upload_batch_descs(mm_batch* b, bool count_only = false) {
   return MM_OK;
 }
 
-// Per-run buffers of the batch's single instance (stage derivatives, stage
-// inputs, workgroup partials and, with FFT demag, the demag field and the
-// spectra) carved from the arena instead of the context's workspace.
-mm_status carve_run_buffers(mm_batch* b, DevArena* ar) {
-  const mm_ctx* c = b->ctxs[0];
+// Per-run buffers of one instance (stage derivatives, stage inputs, workgroup
+// partials and, with FFT demag, the demag field and the spectra that y-z path
+// `path` needs) carved from the arena instead of the context's workspace.
+mm_status carve_run_buffers(const mm_ctx* c, int path, bool xfused, DevArena* ar, mm_batch::RunBufs& r) {
   const Layout& L = c->L;
   const size_t vec = sizeof(float) * 3 * L.S * (size_t)L.ncell;
-  mm_batch::RunBufs& r = b->rb;
   const size_t start = ar->off;
   for (int j = 0; j < 7; ++j)
     if (mm_status s = ar->take(vec, (void**)&r.k[j])) return s;
@@ -882,17 +880,32 @@ mm_status carve_run_buffers(mm_batch* b, DevArena* ar) {
   if (mm_status s = ar->take(sizeof(double) * MMI_PSTRIDE * (size_t)L.nwg, (void**)&r.partials)) return s;
   if (L.fft) {
     const mm_params& p = c->p;
-    if (mm_status s = ar->take(sizeof(float) * 3 * (size_t)L.ncell, (void**)&r.bd)) return s;
-    if (mm_status s = ar->take(sizeof(float2) * (size_t)L.kx * 3 * p.nz * p.ny, (void**)&r.fx)) return s;
+    // With x passes in the stage kernels only the run-start evaluation reads
+    // the demag field from memory, when k_2 (whose place in the k-slot table
+    // never changes) holds nothing yet.
+    static_assert(sizeof(r.k) / sizeof(r.k[0]) == 7, "k_2 is r.k[1]");
+    if (xfused) r.bd = r.k[1];
+    else if (mm_status s = ar->take(sizeof(float) * 3 * (size_t)L.ncell, (void**)&r.bd)) return s;
+    const size_t rows = sizeof(float2) * (size_t)L.kx * 3 * p.nz;
+    if (mm_status s = ar->take(rows * p.ny, (void**)&r.fx)) return s;
     // the y pass's spectra (split y-z paths) or the convolved rows' two terms
-    if (!b->groups.empty() && (b->groups[0].path == PATH_SPLIT || b->groups[0].path == PATH_SPLITX ||
-                               b->groups[0].path == PATH_HALVES))
-      if (mm_status s = ar->take(sizeof(float2) * (size_t)L.kx * 3 * p.nz * L.py, (void**)&r.fy)) return s;
+    const int wide = path == PATH_SPLIT || path == PATH_SPLITX ? L.py : path == PATH_HALVES ? 2 * p.ny : 0;
+    if (wide)
+      if (mm_status s = ar->take(rows * wide, (void**)&r.fy)) return s;
   }
   r.on = true;
   r.lo = (char*)r.k[0];
   r.bytes = ar->off - ((start + 255) & ~(size_t)255);
   return MM_OK;
+}
+
+// Whether the instance on y-z path `path` fits the no-allocation run's array,
+// with room for its tables (tens of kilobytes).
+bool noalloc_fits(const mm_ctx* c, int path, bool xfused) {
+  DevArena cnt;
+  cnt.mode = DevArena::COUNT;
+  mm_batch::RunBufs r;
+  return carve_run_buffers(c, path, xfused, &cnt, r) == MM_OK && cnt.off + 256 * 1024 <= MM_NOALLOC_SCRATCH_BYTES;
 }
 
 // Tables, descriptors and streams of a batch.  With an arena (one instance
@@ -949,12 +962,22 @@ mm_status batch_build(mm_batch* b, DevArena* arena = nullptr) {
       g = &b->groups.back();
       g->nx = c->p.nx; g->ny = c->p.ny; g->nz = c->p.nz;
       g->px = c->L.px; g->py = c->L.py; g->pz = c->L.pz; g->kx = c->L.kx;
+      g->xfused = xfuse_fits(c->p.nx) && c->p.sublattices == 1;
       // Few z planes: the short kernels (see there for both sides' times).
-      // Else the exchange kernel, which holds a whole plane; where that fills a CU's LDS
-      // (128 x 64) or exceeds it (256 x 64), halves are the faster, and 256 x 32
-      // goes with them.  us per launch: 101 planes' worth of 100x60x20 16.4 vs
-      // 18.9, the 128x128x32 film 28.6 vs 53.7 in split passes.
-      g->path = halves_fits(g->py, g->pz, g->kx) && (g->py == 256 || (g->py == 128 && g->pz == 64)) ? PATH_HALVES
+      // Else the exchange kernel, which holds a whole plane; where that takes a
+      // CU to itself (128 x 64) halves, two of which share one, are the faster
+      // but where the planes just fill the CUs, and where it does not fit (256)
+      // so are they beside the split passes.  us per DP45 step, halves vs the
+      // others: 128x128x32 357 vs 480, 128x128x16 235 vs 599, 32x128x16 169 vs
+      // 543; 64x64x32 186 vs 197, three of them 261 vs 242, four 278 vs 358,
+      // twelve 692 vs 757; 200x40x20 264 vs 340; smaller planes 0.85 to 1.12
+      // times the exchange kernel's speed.
+      // Halves keep the convolved rows twice beside X: an instance that would
+      // outgrow the no-allocation run's array with them, which does what other
+      // runs do, stays with the exchange kernel (160x64x32 359 vs 411 us).
+      g->path = halves_fits(g->py, g->pz, g->kx) &&
+                        (g->py == 256 || (g->py == 128 && g->pz == 64 && noalloc_fits(c, PATH_HALVES, g->xfused)))
+                    ? PATH_HALVES
                 : xch_fits(g->ny, g->nz, g->py, g->pz)  ? PATH_XCH
                 : short_fits(g->py, g->pz)              ? PATH_SHORT
                 : reg8_fits(g->ny, g->nz, g->py, g->pz) ? PATH_REG8
@@ -972,14 +995,13 @@ mm_status batch_build(mm_batch* b, DevArena* arena = nullptr) {
     while (tw * 2 <= 16 && 3 * (tw * 2) * g.pz <= 2048) tw *= 2;
     g.TW = tw;
     g.TK = std::max(1, fused_tile(g.ny, g.nz, g.py, g.pz));
-    g.xfused = xfuse_fits(g.nx);
-    for (int m : g.members)
-      if (b->ctxs[m]->p.sublattices != 1) g.xfused = false;
     if (mm_status s = build_group(g, ar)) return s;
   }
   batch_xfused(b);
   if (arena)
-    if (mm_status s = carve_run_buffers(b, ar)) return s;
+    if (mm_status s = b->groups.empty() ? carve_run_buffers(b->ctxs[0], -1, false, ar, b->rb)
+                                        : carve_run_buffers(b->ctxs[0], b->groups[0].path, b->groups[0].xfused, ar, b->rb))
+      return s;
   if (mm_status s = upload_batch_descs(b, counting)) return s;
   if (arena) return MM_OK;
   MM_HIP(hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
