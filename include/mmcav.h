@@ -350,11 +350,12 @@ enum {
 mm_status mm_batch_set_fft_path(mm_batch* b, int32_t path);
 
 /* Strategy of the x passes (R2C forward, C2R inverse) for every FFT grid
- * shape: MM_X_STAGE (the default where it applies: nx a power of two from 2
- * to 256, one sublattice) does them inside the stage kernels, each workgroup
- * for its own whole x-rows, so the demag field never goes through device
- * memory and the next stage input is transformed where it is computed (other
- * nx from 2 to 256 start out this way too, but cannot be set to it again);
+ * shape: MM_X_STAGE (the default where it applies: nx from 2 to 256, one
+ * sublattice) does them inside the stage kernels, each workgroup for its own
+ * whole x-rows, so the demag field never goes through device memory and the
+ * next stage input is transformed where it is computed (where nx is no power
+ * of two it can be asked for once another choice has been made, to return to
+ * the default);
  * MM_X_LDS transforms tiles of rows in separate kernels; MM_X_REGISTER does
  * so with each pair of real rows as one complex line over four lanes in
  * registers (padded x of 16..128 cells only).  Same results to FP32

@@ -492,6 +492,7 @@ struct mm_batch {
     int nx, ny, nz, px, py, pz, kx;
     int path;
     bool xfused = false;   // x passes inside the stage kernels
+    bool x_set = false;    // the caller has chosen their place (mm_batch_set_fft_x)
     bool rides = true;     // finalisations may ride on the first y-z (or y-forward) launch
     int Wx, Wy, TW, TK = 1;
     WorkItem *xf = nullptr, *yz = nullptr, *y = nullptr, *zc = nullptr;
@@ -2802,8 +2803,11 @@ static mm_status check_fft_x(const mm_batch* b, int32_t path) {
   for (auto& g : b->groups) {
     if (path == MM_X_REGISTER && !xreg_fits(g.px))
       return fail(MM_ERR_ARG, "register x path needs a padded x of 16..128 cells");
-    if (path == MM_X_STAGE && (!xfuse_fits(g.nx) || (g.nx & (g.nx - 1))))
-      return fail(MM_ERR_ARG, "x passes in the stage kernels need nx a power of two from 2 to 256");
+    if (path == MM_X_STAGE && !xfuse_fits(g.nx))
+      return fail(MM_ERR_ARG, "x passes in the stage kernels need nx from 2 to 256");
+    // (callers that ask a new batch for it as a test of nx are answered as ever)
+    if (path == MM_X_STAGE && (g.nx & (g.nx - 1)) && !g.x_set)
+      return fail(MM_ERR_ARG, "x passes in the stage kernels are this nx's default, to which only another choice can return");
     if (path == MM_X_STAGE)
       for (int m : g.members)
         if (b->ctxs[m]->p.sublattices != 1) return fail(MM_ERR_ARG, "x passes in the stage kernels need one sublattice");
@@ -2821,6 +2825,7 @@ mm_status mm_batch_set_fft_x(mm_batch* b, int32_t path) {
   MM_HIP(hipStreamSynchronize(b->stream));
   for (auto& g : b->groups) {
     g.xfused = path == MM_X_STAGE;
+    g.x_set = true;
     g.Wx = path == MM_X_REGISTER ? 0 : std::max(1, std::min(16, 1024 / g.px));
     if (mm_status s = build_group(g)) return s;
   }
