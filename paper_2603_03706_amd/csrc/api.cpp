@@ -471,6 +471,10 @@ struct mm_batch {
     std::vector<int> members;
   };
   std::vector<Small> small;
+  // streams for launches of small instances beside those on `stream`, made when first needed
+  hipStream_t side[3] = {};
+  hipEvent_t side_fork = nullptr, side_join[3] = {};
+  bool side_used[3] = {};
   int* d_flags = nullptr;
   int* h_flags = nullptr;
   int h_flags_local[2] = {0, 0};   // host flags of a batch without pinned memory (no-allocation run)
@@ -1181,23 +1185,90 @@ mm_status enqueue_stage(mm_batch* b, int st, bool with_final = true) {
   });
 }
 
-// `steps` steps of the small instances, at most kSmallSteps per launch.
-mm_status enqueue_small(mm_batch* b, int64_t steps) {
+// The small instances of one kind: those of a group with or without profiles.
+struct SmallLaunch {
+  const mm_batch::Small* g;
+  bool prof;
+  size_t lds;
+  long long weight;   // roughly in proportion to a step's time
+};
+std::vector<SmallLaunch> small_launches(const mm_batch* b) {
+  std::vector<SmallLaunch> out;
   for (const auto& g : b->small)
     for (const bool prof : {false, true}) {
       size_t lds = 0;
+      int modes = 0;
       for (int m : g.members) {
         const InstDesc& d = b->ctxs[m]->desc;
-        if ((d.profiled != 0) == prof) lds = std::max(lds, small_lds(d.S, d.ncell, prof ? d.N : 0));
+        if ((d.profiled != 0) != prof) continue;
+        lds = std::max(lds, small_lds(d.S, d.ncell, prof ? d.N : 0));
+        modes = std::max(modes, d.N);
       }
-      if (!lds) continue;
-      for (int64_t left = steps; left > 0; left -= kSmallSteps)
-        if (mm_status s = launch(b, "small_rk4", [&] {
-              return mmk_launch_small_rk4(g.S, g.ncell, prof, (int)g.members.size(), lds, b->d_desc, g.list,
-                                          (int)std::min<int64_t>(left, kSmallSteps), b->stream);
-            }))
-          return s;
+      if (lds) out.push_back({&g, prof, lds, (long long)g.per * (2 * g.S + (prof ? 2 * modes : 0))});
     }
+  return out;
+}
+
+// `steps` steps of them on stream s, at most kSmallSteps per launch.
+mm_status launch_small(mm_batch* b, const SmallLaunch& l, int64_t steps, hipStream_t s) {
+  for (int64_t left = steps; left > 0; left -= kSmallSteps)
+    if (mm_status st = launch(b, "small_rk4", [&] {
+          return mmk_launch_small_rk4(l.g->S, l.g->ncell, l.prof, (int)l.g->members.size(), l.lds, b->d_desc, l.g->list,
+                                      (int)std::min<int64_t>(left, kSmallSteps), s);
+        }))
+      return st;
+  return MM_OK;
+}
+
+// `steps` steps of the small instances, one kind after the other.
+mm_status enqueue_small(mm_batch* b, int64_t steps) {
+  for (const SmallLaunch& l : small_launches(b))
+    if (mm_status s = launch_small(b, l, steps, b->stream)) return s;
+  return MM_OK;
+}
+
+// The same with the kinds beside each other and beside what follows on the
+// batch's stream until join_small: a launch of a few workgroups leaves the rest
+// of the device to the others, which would otherwise wait for it (and did not
+// have to where all instances shared the per-stage launches).  us per RK4 step,
+// one after the other / beside each other / per-stage launches for all: the
+// 64x64x16 film with one 2048-cell instance of sixteen profiled modes
+// 193 / 102 / 142, 2049 cells with the same 130 / 98 / 117, with forty 2048-cell
+// instances of one mode 41 / 32 / 34; six kinds of 64 to 2048 cells 235 / 104 / 123,
+// two hundred of each 429 / 380 / 464.
+mm_status fork_small(mm_batch* b, int64_t steps) {
+  constexpr int NS = 3;
+  std::vector<SmallLaunch> ls = small_launches(b);
+  if (ls.size() + (b->gen_wg ? 1 : 0) <= 1) return enqueue_small(b, steps);
+  std::sort(ls.begin(), ls.end(), [](const SmallLaunch& x, const SmallLaunch& y) { return x.weight > y.weight; });
+  if (!b->side_fork) MM_HIP(hipEventCreateWithFlags(&b->side_fork, hipEventDisableTiming));
+  MM_HIP(hipEventRecord(b->side_fork, b->stream));
+  long long load[NS + 1] = {};   // the last: the batch's own stream, for these where it has no step graphs
+  for (const SmallLaunch& l : ls) {
+    int q = 0;
+    for (int k = 1; k < (b->gen_wg ? NS : NS + 1); ++k)
+      if (load[k] < load[q]) q = k;
+    load[q] += l.weight;
+    if (q == NS) {
+      if (mm_status s = launch_small(b, l, steps, b->stream)) return s;
+      continue;
+    }
+    if (!b->side[q]) MM_HIP(hipStreamCreateWithFlags(&b->side[q], hipStreamNonBlocking));
+    if (!b->side_join[q]) MM_HIP(hipEventCreateWithFlags(&b->side_join[q], hipEventDisableTiming));
+    if (!b->side_used[q]) MM_HIP(hipStreamWaitEvent(b->side[q], b->side_fork, 0));
+    b->side_used[q] = true;
+    if (mm_status s = launch_small(b, l, steps, b->side[q])) return s;
+  }
+  return MM_OK;
+}
+
+mm_status join_small(mm_batch* b) {
+  for (int q = 0; q < 3; ++q) {
+    if (!b->side_used[q]) continue;
+    b->side_used[q] = false;
+    MM_HIP(hipEventRecord(b->side_join[q], b->side[q]));
+    MM_HIP(hipStreamWaitEvent(b->stream, b->side_join[q], 0));
+  }
   return MM_OK;
 }
 
@@ -1326,23 +1397,34 @@ mm_status launch_steps(mm_batch* b, int64_t steps) {
       if ((steps % kStepsPerGraph) >> lg & 1)
         if (mm_status s = ensure_graph_pow(p, lg)) return s;
   }
-  for (int64_t left = steps; left >= kStepsPerGraph; left -= kStepsPerGraph)
+  hipError_t e = hipSuccess;
+  mm_status st = MM_OK;
+  for (mm_batch* p : seq)
+    if (st == MM_OK) st = fork_small(p, steps);
+  for (int64_t left = st == MM_OK ? steps : 0; left >= kStepsPerGraph; left -= kStepsPerGraph)
     for (mm_batch* p : seq)
-      if (p->gen_wg) MM_HIP(hipGraphLaunch(p->exec, p->stream));
-  for (int lg = 4; lg >= 0; --lg)
+      if (p->gen_wg && e == hipSuccess) e = hipGraphLaunch(p->exec, p->stream);
+  for (int lg = 4; lg >= 0 && st == MM_OK; --lg)
     if ((steps % kStepsPerGraph) >> lg & 1)
       for (mm_batch* p : seq)
-        if (p->gen_wg) MM_HIP(hipGraphLaunch(p->exec_pow[lg], p->stream));
-  for (mm_batch* p : seq)
-    if (mm_status s = enqueue_small(p, steps)) return s;
-  return MM_OK;
+        if (p->gen_wg && e == hipSuccess) e = hipGraphLaunch(p->exec_pow[lg], p->stream);
+  for (mm_batch* p : seq) {
+    const mm_status s = join_small(p);
+    if (st == MM_OK) st = s;
+  }
+  MM_HIP(e);
+  return st;
 }
 
 // The next piece of a run to an end time: one step graph, and as many steps
 // of the small instances (which run on by themselves where they are alone).
 mm_status launch_piece(mm_batch* b) {
-  if (b->gen_wg) MM_HIP(hipGraphLaunch(b->exec, b->stream));
-  return enqueue_small(b, b->gen_wg ? kStepsPerGraph : kSmallSteps);
+  mm_status st = fork_small(b, b->gen_wg ? kStepsPerGraph : kSmallSteps);
+  const hipError_t e = b->gen_wg && st == MM_OK ? hipGraphLaunch(b->exec, b->stream) : hipSuccess;
+  const mm_status s = join_small(b);
+  if (st == MM_OK) st = s;
+  MM_HIP(e);
+  return st;
 }
 
 // One reverse step of the discrete adjoint for every instance of the batch
@@ -3234,6 +3316,11 @@ mm_status mm_batch_destroy(mm_batch* b) {
   if (b->d_flags) hipFree(b->d_flags);
   if (b->h_flags) hipHostFree(b->h_flags);
   if (b->ev) hipEventDestroy(b->ev);
+  for (int q = 0; q < 3; ++q) {
+    if (b->side_join[q]) hipEventDestroy(b->side_join[q]);
+    if (b->side[q]) hipStreamDestroy(b->side[q]);
+  }
+  if (b->side_fork) hipEventDestroy(b->side_fork);
   if (b->stream) hipStreamDestroy(b->stream);
   delete b;
   return MM_OK;

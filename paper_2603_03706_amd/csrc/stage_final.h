@@ -468,11 +468,11 @@ template <int METHOD, int ST>
 __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double* tot) {
   const InstDesc& D = descs[inst];
   InstCtl* C = D.ctl;
+  if (METHOD == MMI_RK4 && ST >= 1 && D.small) return;   // (k_small_rk4 may be at work on it)
   if (C->done) {
     if (METHOD == MMI_RK4 && ST == 3 && threadIdx.x == 0) C->idle = 1;
     return;
   }
-  if (METHOD == MMI_RK4 && ST >= 1 && D.small) return;
   const bool has_next = !(METHOD == MMI_DP45 && ST == 7);
   const double scale = D.inv_ngeo / (double)D.S;
   // the slots this stage needs, dealt to the waves as one list so that the
