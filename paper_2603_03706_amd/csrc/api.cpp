@@ -1300,8 +1300,8 @@ mm_status enqueue_start(mm_batch* b) {
 // (see below for that one) runs as extra workgroups of the next stage's first y-z (or y-forward)
 // launch: the transform reads and writes only X (and Y), which the
 // finalisation does not touch, and of the control block the flag that says
-// whether the run is over, which is one that no finalisation in the launch
-// sets (transform_idle); the next stage kernel comes after both in stream
+// whether the run is over, which is one that the stage kernels set
+// (transform_idle); the next stage kernel comes after both in stream
 // order.
 bool merge_final(const mm_batch* b) { return !b->groups.empty() && b->groups[0].rides; }
 
@@ -2668,7 +2668,7 @@ static mm_status adjoint_impl(mm_ctx* c, const double* dL_da, const float* dL_dm
     // reverse the segment
     h.rec_index = (int)steps - 1;
     h.adj_base = (long long)k * K;
-    h.done = 0;
+    h.done = h.idle = 0;
     h.adj_h = c->rec_h;
     h.adj_t0 = c->ck_ctl[k].t;
     if (mm_status s = ctl_push(c, h)) return s;
@@ -3110,7 +3110,7 @@ static mm_status tune_fft(mm_batch* b, std::string& out) {
   for (mm_ctx* c : b->ctxs) {
     InstCtl h;
     if (mm_status s = ctl_pull(c, h)) return s;
-    h.done = 0;
+    h.done = h.idle = 0;
     if (mm_status s = ctl_push(c, h)) return s;
   }
   if (mm_status s = refresh_descs(b)) return s;

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(MM_YZ_T) void k_fft_yz(const InstDesc* __restrict__
   }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   const int kx = wi.item;
   const int ny = D.ny, nz = D.nz, Py = D.py, Pz = D.pz;
   const int RP = Py + 1;
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(MM_YZR_T, 2) void k_fft_yzr(const InstDesc* __restr
   load_twiddles(tw32, 32, tw, MM_YZR_T);
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   const int kx = wi.item;
   const int ny = D.ny, nz = D.nz;
   const int nrow = 3 * nz;
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(MM_YZ8_T) __attribute__((amdgpu_waves_per_eu(4, 4))
   load_twiddles(tw32, 32, tw, MM_YZ8_T);
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   const int kx = wi.item;
   const int ny = D.ny, nz = D.nz;
   const int nrow = 3 * nz;
@@ -1088,7 +1088,7 @@ __global__ __launch_bounds__(MM_YZX_T) __attribute__((amdgpu_waves_per_eu(MY >= 
   }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   if constexpr (YzxPairs<4 * MY, 4 * MZ>::on) {
     if (wi.item == 0 && D.kx > 1) {
       yzx_item<MY, MZ, RPAD, true>(D, 0, tw, lds);
@@ -1388,7 +1388,7 @@ __global__ __launch_bounds__((YzHalf<M, PZ>::T)) __attribute__((amdgpu_waves_per
   const int q = nyz >> 3, rem = nyz & 7, b = blockIdx.x, xcd = b & 7;
   const WorkItem wi = work[xcd * q + min(xcd, rem) + (b >> 3)];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   if (wi.item < 2) yzh_item<M, PZ, true>(D, 0, wi.item, tw, lds);
   else yzh_item<M, PZ, false>(D, wi.item >> 1, wi.item & 1, tw, lds);
 }
@@ -1427,7 +1427,7 @@ __global__ __launch_bounds__(MM_SX_T) void k_fft_ysx(const InstDesc* __restrict_
   load_twiddles(twy, PY, tw, MM_SX_T);
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   const int ny = D.ny, nlines = D.kx * 3 * D.nz;
   const int l0 = wi.item * ROWS;
   const int nr = min(ROWS, nlines - l0);
@@ -1622,7 +1622,7 @@ __global__ __launch_bounds__(256) void k_fft_y(const InstDesc* __restrict__ desc
   }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   const int ny = D.ny, Py = D.py;
   const int nlines = D.kx * 3 * D.nz;
   const int l0 = wi.item * W;

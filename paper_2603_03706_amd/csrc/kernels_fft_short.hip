@@ -48,7 +48,7 @@ __global__ __launch_bounds__((YzShort<PY, PZ>::T)) void k_fft_yzs(const InstDesc
   }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   float2* B = lds;                              // rows [3][ZR][PY + 1]
   float2* twy = B + 3 * ZR * RS;
   float2* twz = twy + PY;
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(YThin<M>::T) void k_fft_y1(const InstDesc* __restri
   }
   const WorkItem wi = work[blockIdx.x];
   const InstDesc& D = descs[wi.inst];
-  if (transform_idle(D, fmethod, fstage)) return;
+  if (transform_idle(D)) return;
   float2* B = lds;                              // lines [2 component + parity][M + 1]
   float2* twm = B + 6 * RS;
   const int ny = D.ny, kx = wi.item;

@@ -103,7 +103,10 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
   const InstDesc& D = descs[wg_inst[lblk]];
   // the control block is only read here (the finalisation kernel writes it)
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
-  if (C->done) return;
+  if (C->done) {
+    if (lblk == D.wg0 && threadIdx.x == 0) D.ctl->idle = 1;   // (see transform_idle)
+    return;
+  }
   const int lw = zmajor_wg(D, lblk - D.wg0);
   const int nc = D.ncell;
   const int i = wg_cell(D, lw);

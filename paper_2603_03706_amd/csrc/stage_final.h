@@ -469,10 +469,7 @@ __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double*
   const InstDesc& D = descs[inst];
   InstCtl* C = D.ctl;
   if (METHOD == MMI_RK4 && ST >= 1 && D.small) return;   // (k_small_rk4 may be at work on it)
-  if (C->done) {
-    if (METHOD == MMI_RK4 && ST == 3 && threadIdx.x == 0) C->idle = 1;
-    return;
-  }
+  if (C->done) return;
   const bool has_next = !(METHOD == MMI_DP45 && ST == 7);
   const double scale = D.inv_ngeo / (double)D.S;
   // the slots this stage needs, dealt to the waves as one list so that the
@@ -487,17 +484,11 @@ __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double*
 }
 
 // Whether a transform has nothing to do because its instance's run is over.
-// method, st: of the finalisation whose stage the launch follows (-1: none),
-// which may ride in it.  An RK4 step's last one sets `done` while the
-// transform's wavefronts run, and those of one workgroup would not all see
-// the same; a launch behind it goes by `idle`, which the finalisation of stage
-// 3 sets, one launch that reads `done` and at most a step later, so that an
-// ended instance is transformed once more (its rows are formed anew by the
-// next run).  Those of the other stages that ride leave `done` alone.
-__device__ __forceinline__ bool transform_idle(const InstDesc& D, int method, int st) {
-  const MMG InstCtl* C = gbl(D.ctl);
-  return (method == MMI_RK4 && st == 4 ? C->idle : C->done) != 0;
-}
+// The finalisation of an RK4 step's last stage sets `done` and may ride in the
+// transform's launch, whose wavefronts would not all see the same of it.  They
+// go by `idle`, which the next stage kernel sets: an ended instance is
+// transformed once more (its rows are formed anew by the next run).
+__device__ __forceinline__ bool transform_idle(const InstDesc& D) { return gbl(D.ctl)->idle != 0; }
 
 // the same as final_body with the method and stage chosen at run time
 __device__ __forceinline__ void final_any(int method, int st, const InstDesc* __restrict__ descs, int inst,
