@@ -416,8 +416,12 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
 }
 
 // ------------------------------------------------------------ stage B
+// Stages 2 to 4 of the DP45 replay read up to four stored mu beside the
+// stencil and need 68 to 76 registers: held to eight wavefronts per SIMD they
+// spilled 9, 13 and 1, which made a reverse step up to 1.7 % longer (two
+// sublattices, 128x128x16 cells: 1010 vs 993 us; nowhere shorter).
 template <bool DP, int ST>
-__global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(8), amdgpu_num_sgpr(80))) void k_adj_b(const InstDesc* __restrict__ descs,
+__global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_waves_per_eu(DP && ST >= 2 && ST <= 4 ? 6 : 8), amdgpu_num_sgpr(80))) void k_adj_b(const InstDesc* __restrict__ descs,
                                                   const int* __restrict__ wg_inst,
                                                   const float2* __restrict__ tw, int nblocks, int count) {
   __shared__ double tot[MMI_PSTRIDE];
