@@ -41,9 +41,10 @@ constexpr double kMu0 = 4e-7 * M_PI;
 mm_status open_error() { return fail(MM_ERR_STATE, "the instance is in an open batch run (mm_batch_end first)"); }
 
 constexpr int kStepsPerGraph = 32;
-// Steps per launch of the whole-step kernel: a few milliseconds of work (it
-// ends by itself when its instances are done), so that the host's look at
-// the done flags between launches does not show.
+// Steps per launch of the whole-step kernel: 2 ms of work for 64 cells, 11 for
+// 2048, 100 with sixteen profiled modes (it ends by itself when its instances
+// are done), so that the host's look at the done flags between launches does
+// not show.
 constexpr int kSmallSteps = 1024;
 // Sub-batches (streams) a new batch runs as; mm_batch_tune may choose more.
 constexpr int kDefaultParts = 1;
@@ -200,8 +201,11 @@ constexpr int XR_ROWS = 128;
 // x-rows of each component, so nx is from 2 to MMI_WG / 2.  It takes the
 // largest power of two of rows; for other nx than powers of two up to half its
 // threads then have no cell, but the two launches and passes through memory
-// per evaluation that the separate x kernels cost are worth more: 100x60x20,
-// RK4, 143 vs 170 us per step, 200x200x1, DP45, 252 vs 286 us.
+// per evaluation that the separate x kernels cost are worth more.  us per DP45
+// step, ny x nz = 32 x 16, one instance and eight: nx = 3 106 vs 131 and 107 vs
+// 140, 65 128 vs 167 and 304 vs 361, 129 (half the threads) 162 vs 219 and 576
+// vs 617, 255 170 vs 224 and 587 vs 668; sixteen of 64 x 16: 33 478 vs 571, 129
+// 2098 vs 2112, 200 2208 vs 2306.
 bool xfuse_fits(int nx) { return nx >= 2 && nx <= MMI_WG / 2; }
 int xfuse_lg_rows(int nx) {
   int lg = 0;
@@ -1462,8 +1466,8 @@ mm_status enqueue_reverse_step(mm_batch* b) {
 // workgroup vs the graph of nine launches: 64 cells 9.6 vs 47, 512 cells 13 vs
 // 56 (two sublattices 19 vs 75, these with sixteen profiled modes 71 vs 189),
 // 1024 cells 23 vs 59 (two sublattices 45 vs 82, these with sixteen modes 180
-// vs 227); with four cells per thread the adjoint vectors no longer fit in
-// registers: 62 vs 66, with sixteen modes 326 vs 264.
+// vs 227); with four cells per thread most of the adjoint vectors are in
+// scratch memory: 62 vs 66, with sixteen modes 326 vs 264.
 // LDS: a stage input and lambda_B, then grad u and the profiles where they fit.
 bool small_reverse(const mm_batch* b) {
   const mm_ctx* c = b->ctxs[0];

@@ -101,14 +101,6 @@ __device__ __forceinline__ int xslot(int k1, int a) {
   return k1 * L + ((a + k1) & (L - 1));
 }
 
-// order the wavefront's LDS accesses across lanes (no instruction: a
-// wavefront's LDS operations already complete in issue order)
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.y); }
 
 // The y transforms of one row held in LDS by N lanes (lane lam).  Forward:

@@ -59,12 +59,6 @@ struct AdjSums {
   }
 };
 
-__device__ __forceinline__ void cross3(const float* a, const float* b, float* o) {
-  o[0] = a[1] * b[2] - a[2] * b[1];
-  o[1] = a[2] * b[0] - a[0] * b[2];
-  o[2] = a[0] * b[1] - a[1] * b[0];
-}
-
 // size of the step being reversed: fixed (RK4) or the logged one (DP45)
 template <class CtlPtr>
 __device__ __forceinline__ double adj_step(const InstDesc& D, CtlPtr C) {

@@ -1113,11 +1113,13 @@ __global__ __launch_bounds__(MM_YZX_T) __attribute__((amdgpu_waves_per_eu(MY >= 
 // Items write to D.fy ([r][kx][c][z][y], y < ny): both read the same X.
 //
 // What bounds it: the phases of one workgroup (256 x 64: 153 KB of LDS, one per
-// CU), which the launch is a single round of.  Of an ordinary item's 19 us at
-// 128 x 128 x 32 cells 3.7 go to loading rows and kernel values, 3.1 to each y
-// pass, 6 to the z convolution, 2.3 to the store; vector issue alone would be 13.
-// The launch (28.6 us against 53.7 for the three split passes, which moved
-// the padded spectra through memory twice) waits for the two items that carry
+// CU), which the launch is a single round of, at 128 registers of which 8 to
+// 23 are spilled.  Of an ordinary item's 19 us at 128 x 128 x 32 cells 3.7 go
+// to loading rows and kernel values, 3.1 to each y pass, 6 to the z
+// convolution, 2.3 to the store; vector issue alone would be 13.
+// The launch (28.6 us repeated by itself, 31 within a step, against 53.7 by
+// themselves for the three split passes, which moved the padded spectra through
+// memory twice) waits for the two items that carry
 // the real planes: separating and rebuilding their half spectra and the
 // second kernel slice make them a third longer.  Reading that slice from
 // memory in the multiply (38 us), or replacing the first one in LDS between

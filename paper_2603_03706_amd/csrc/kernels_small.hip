@@ -5,7 +5,10 @@
 // step, and a launch per stage and finalisation (eight per step) cost it
 // about 30 us.  Here one workgroup owns the instance for as many steps as
 // the launch is given: the state and the running sum of the stage
-// derivatives stay in registers, the stage inputs are exchanged through LDS
+// derivatives stay with their threads (in registers; with more than one cell
+// per thread, at the three wavefronts per SIMD of such a workgroup, in part in
+// scratch memory: 14 to 20 spilled registers for two cells, 77 to 107 for
+// four), the stage inputs are exchanged through LDS
 // (two buffers, one barrier per stage), and one further wavefront carries
 // the FP64 cavity modes, one per lane, beside the cell wavefronts.
 //
@@ -27,8 +30,8 @@
 // envelope's exponential, a division by 6 and the loads of the descriptor on
 // the cavity's chain, took 7.8 and 11.5 ms.
 // The arithmetic and the order of every sum are those of k_stage and
-// finalize, so an instance's results do not depend on which of the two
-// carries it.
+// finalize, with shared functions whose fused multiply-adds are written out:
+// an instance's results do not depend on the batch it is in.
 #include <type_traits>
 #include "mm_internal.h"
 #include "kernels_common.h"
@@ -354,12 +357,12 @@ __device__ __forceinline__ void small_cavity(const InstDesc& D, SmallShared<C>& 
     if (coupled) {
       ModeDesc MC = MD;
       MC.jcpl_on = 1;
-      wave_order();
+      wave_lds_order();
       if (mode) {
         sh.amp[n][0] = v.r;
         sh.amp[n][1] = v.i;
       }
-      wave_order();
+      wave_lds_order();
       cav_rhs(MC, n, ts, sh.amp, mv.r, mv.i, f.r, f.i);
     }
     return f;

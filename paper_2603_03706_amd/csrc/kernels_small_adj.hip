@@ -5,7 +5,8 @@
 // B per stage: nine a step) cost an instance of at most 1024 cells without
 // FFT demag the launch each, as its forward steps did.  Here one
 // workgroup runs any number of reverse steps: the adjoints lambda_y, lambda_z
-// and lambda_k of a cell stay in registers, its stage input and lambda_B are
+// and lambda_k of a cell stay with its thread (in registers, but for two
+// sublattices with two cells per thread, which spill 61), its stage input and lambda_B are
 // exchanged through LDS, the recorded stage inputs are fetched one stage
 // ahead, and one further wavefront carries the cavity part, one mode per lane.
 // A stage has two barriers: behind A (lambda_B and the wave sums are in LDS)
@@ -17,7 +18,10 @@
 // A reverse step of the 8x8x1 geometry with the recompute of its forward step:
 // 9.6 us against 46.9 us in per-stage launches; the gradient of 256 of its
 // steps through the autograd function 4.9 against 14.8 ms.
-// The arithmetic and the order of every sum are those of the per-stage kernels.
+// The order of every sum is that of the per-stage kernels; the terms of mu_a
+// are added in another order and the compiler contracts the rest as it likes,
+// so the two agree to rounding.  Which of them an instance takes depends on it
+// alone.
 #include "mm_internal.h"
 #include "kernels_common.h"
 #include "launch.h"
@@ -36,12 +40,6 @@ struct AdjShared {
   float fb[MMI_MAX_MODES], fbw[MMI_MAX_MODES];  // feedback weights of the stage: in the field, in grad u_n
   float lr[MMI_MAX_MODES], li[MMI_MAX_MODES];   // adjoint of m^-
 };
-
-__device__ __forceinline__ void cross(const float (&a)[3], const float (&b)[3], float (&o)[3]) {
-  o[0] = a[1] * b[2] - a[2] * b[1];
-  o[1] = a[2] * b[0] - a[0] * b[2];
-  o[2] = a[0] * b[1] - a[1] * b[0];
-}
 
 // Cell wavefronts.  sm: [S][512 C] stage input, [S][512 C] lambda_B (16-byte
 // entries, so that a neighbour is one read), then [N][ncell] grad u_n (double)
@@ -187,15 +185,15 @@ __device__ __forceinline__ void adj_cells(const InstDesc& D, AdjShared<C>& sh, f
           float B[3], P[3], R[3], lm[3], t1[3], t2[3], t3[3];
           field_nb(Q, i, nb[s], m, s, fb, false, B);
           const float(&l)[3] = lk[j][s];
-          cross(m[s], B, P);
-          cross(m[s], P, R);
-          cross(l, m[s], lm);         // lambda x m
-          cross(lm, m[s], t1);        // (lambda x m) x m
+          cross3(m[s], B, P);
+          cross3(m[s], P, R);
+          cross3(l, m[s], lm);         // lambda x m
+          cross3(lm, m[s], t1);        // (lambda x m) x m
 #pragma unroll
           for (int c = 0; c < 3; ++c) lb[j][s][c] = mag[j] ? -gl * (lm[c] + al * t1[c]) : 0.f;
-          cross(B, l, t1);            // B x lambda
-          cross(P, l, t2);            // P x lambda
-          cross(B, lm, t3);           // B x (lambda x m)
+          cross3(B, l, t1);            // B x lambda
+          cross3(P, l, t2);            // P x lambda
+          cross3(B, lm, t3);           // B x (lambda x m)
           // dL/dalpha: lambda . (-(2a/(1+a^2)) tau - gamma' R), tau = -gamma' (P + a R)
           float ga = 0.f;
 #pragma unroll
@@ -403,12 +401,12 @@ __device__ __forceinline__ void adj_cavity(const InstDesc& D, AdjShared<C>& sh, 
       mur += Li * lka[0] - Lr * lka[1];
       mui -= Lr * lka[0] + Li * lka[1];
       if (coupled) {
-        wave_order();
+        wave_lds_order();
         if (mode) {
           sh.lk[n][0] = lka[0];
           sh.lk[n][1] = lka[1];
         }
-        wave_order();
+        wave_lds_order();
         for (int q = 0; q < N; ++q) {
           // -i sum_q J_qn a_n in the equation of mode q, J symmetric
           mur -= D.jcpl[q][n] * sh.lk[q][1];

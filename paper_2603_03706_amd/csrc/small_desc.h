@@ -20,11 +20,4 @@ struct CellDesc {
         alpha(D.alpha), csign{D.csign[0], D.csign[1]}, bd(nullptr) {}
 };
 
-// orders LDS accesses of the lanes of one wavefront (they complete in issue order)
-__device__ __forceinline__ void wave_order() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 }  // namespace mmk
