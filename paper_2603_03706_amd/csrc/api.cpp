@@ -1304,8 +1304,8 @@ mm_status enqueue_start(mm_batch* b) {
 // (see below for that one) runs as extra workgroups of the next stage's first y-z (or y-forward)
 // launch: the transform reads and writes only X (and Y), which the
 // finalisation does not touch, and of the control block the flag that says
-// whether the run is over, which is one that the stage kernels set
-// (transform_idle); the next stage kernel comes after both in stream
+// whether the run is over, which is one that no finalisation sets while it
+// rides (transform_idle); the next stage kernel comes after both in stream
 // order.
 bool merge_final(const mm_batch* b) { return !b->groups.empty() && b->groups[0].rides; }
 

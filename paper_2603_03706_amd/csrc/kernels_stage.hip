@@ -104,7 +104,7 @@ __global__ __launch_bounds__(MMI_WG) __attribute__((amdgpu_num_sgpr(80))) void k
   // the control block is only read here (the finalisation kernel writes it)
   const MMG InstCtl* __restrict__ C = gbl(D.ctl);
   if (C->done) {
-    if (lblk == D.wg0 && threadIdx.x == 0) D.ctl->idle = 1;   // (see transform_idle)
+    if (METHOD == MMI_RK4 && ST == 1 && lblk == D.wg0 && threadIdx.x == 0) D.ctl->idle = 1;   // (see transform_idle)
     return;
   }
   const int lw = zmajor_wg(D, lblk - D.wg0);
@@ -372,6 +372,10 @@ __global__ __launch_bounds__(MMI_WG) void k_final(const InstDesc* __restrict__ d
   __shared__ double tot[MMI_PSTRIDE];
   if ((int)blockIdx.x >= count) return;
   final_body<METHOD, ST>(descs, blockIdx.x, tot);
+  if (METHOD == MMI_RK4 && ST == 4 && threadIdx.x == 0) {   // (no transform runs beside this launch)
+    const InstDesc& D = descs[blockIdx.x];
+    if (!D.small && D.ctl->done) D.ctl->idle = 1;
+  }
 }
 
 }  // namespace mmk

@@ -31,7 +31,7 @@ struct InstCtl {
   double dt_min_seen, dt_max_seen;
   long long accepted, rejected;
   int status, done, cur, clipped, last_rejected;
-  int idle;                           // set by the stage kernels once they have seen `done` (see transform_idle)
+  int idle;                           // `done`, but never set beside a transform (see transform_idle)
   int slot[8];                        // physical k-buffer of stage derivative j
   double a[MMI_MAX_MODES][2];         // cavity amplitudes at the step start
   double as[MMI_MAX_MODES][2];        // cavity value feeding the next stage kernel

@@ -424,7 +424,7 @@ __device__ void finalize(const InstDesc& D, InstCtl* C, const double* tot) {
     C->slot[6] = s0;
     if (C->replay) {
       if (C->replay_idx >= C->replay_end || C->t >= C->t_end) {
-        C->done = 1;
+        C->done = C->idle = 1;
       } else {
         plan_replay(D, C);
         const double hh = C->h;
@@ -449,10 +449,10 @@ __device__ void finalize(const InstDesc& D, InstCtl* C, const double* tot) {
   if (C->dt_max > 0.0) dtn = fmin(dtn, C->dt_max);
   C->dt = dtn;
   if (C->t >= C->t_end) {
-    C->done = 1;
+    C->done = C->idle = 1;
   } else if (dtn < C->dt_min) {
     C->status = finite ? -5 : -6;
-    C->done = 1;
+    C->done = C->idle = 1;
   }
   plan_step(C, dtn);
   const double hh = C->h;
@@ -486,8 +486,10 @@ __device__ void final_body(const InstDesc* __restrict__ descs, int inst, double*
 // Whether a transform has nothing to do because its instance's run is over.
 // The finalisation of an RK4 step's last stage sets `done` and may ride in the
 // transform's launch, whose wavefronts would not all see the same of it.  They
-// go by `idle`, which the next stage kernel sets: an ended instance is
-// transformed once more (its rows are formed anew by the next run).
+// go by `idle`, which is set with `done` where the finalisation has a launch of
+// its own (as a DP45 step's last always has), else by the stage kernel behind
+// it: the ended instance is then transformed once more (its rows are formed
+// anew by the next run).
 __device__ __forceinline__ bool transform_idle(const InstDesc& D) { return gbl(D.ctl)->idle != 0; }
 
 // the same as final_body with the method and stage chosen at run time

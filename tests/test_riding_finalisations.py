@@ -37,8 +37,11 @@ def test_transforms_that_carry_finalisations_do_not_read_done():
     for name, body in riding.items():
         assert "done" not in body, name
         assert "transform_idle(D)" in body, name
-    final = open(os.path.join(CSRC, "stage_final.h")).read()
-    assert not re.search(r"->idle\s*=", final)
+    # the finalisation itself sets that flag in adaptive runs only, whose step end never rides
+    rk4, dp45 = open(os.path.join(CSRC, "stage_final.h")).read().split("-- DP45\n")
+    assert not re.search(r"idle\s*=", rk4) and dp45.count("C->done = C->idle = 1;") == dp45.count("C->done =")
+    api = open(os.path.join(CSRC, "api.cpp")).read()
+    assert re.search(r"bool merge_step_end\(const mm_batch\* b\) \{\n  if \(b->method != MM_RK4", api)
 
 
 @pytest.mark.gpu
