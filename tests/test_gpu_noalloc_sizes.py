@@ -11,9 +11,9 @@ pytestmark = pytest.mark.gpu
 
 # padded y-z of 128 x 64 from where the halved strategy outgrows the array up
 # to where the exchange strategy does; grids it takes with halves; 256 rows in
-# halves; separate x passes
+# halves; separate x passes; split y-z passes
 @pytest.mark.parametrize("grid", [(129, 64, 32), (160, 64, 32), (219, 64, 32), (128, 64, 32), (200, 40, 20),
-                                  (30, 100, 20), (300, 40, 9)])
+                                  (30, 100, 20), (300, 40, 9), (4, 100, 40)])
 @pytest.mark.parametrize("method", ["rk4", "dp45"])
 def test_noalloc_equals_run(grid, method):
     inst = W.Instance(grid=grid, cell=(5e-9, 4e-9, 3e-9), Ms=140e3, Aex=3.65e-12, alpha=0.01, B0=(0.01, 0.0, 0.25),
